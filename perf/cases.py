@@ -109,7 +109,7 @@ def _inputs(case, seed):
     if k == "adj":
         m, x, u = W.adjoint_systems(ns, npl, seed)
     else:
-        m, x, u = W.encounter_systems(ns, npl, seed, da=0.03, dphase=0.3)
+        m, x, u = _crowded(ns, npl, seed)
     # democratic velocities, and the loss gradient at the end
     v = u - (m[..., None] * u).sum(1, keepdims=True) / (1.0 + m.sum(1))[:, None, None]
     r = np.random.default_rng(seed)
@@ -129,6 +129,19 @@ def _systems(nsys, nmax, seed):
     a, e, inc = r.uniform(0.3, 3.0, n), W.rayleigh(r, 0.02, n), W.rayleigh(r, 0.02, n)
     x, u = W.elements_to_cartesian(1.0 + m, a, e, inc, *(W.TWO_PI * r.random((3, n))))
     return {"off": off, "m0s": np.ones(nsys), "m": m, "x": x, "u": u}
+
+
+def _crowded(nsys, npl, seed):
+    """Planets close enough to meet, as workloads.encounter_systems draws
+    them, but warmer and wider: about one system in ten has an encounter in a
+    step, and none so deep that the gradient is refused."""
+    r, n = W.rng_for(seed), nsys * npl
+    m = np.exp(r.uniform(np.log(1e-8), np.log(1e-6), n))
+    a, e, inc = r.uniform(0.9, 1.1, n), W.rayleigh(r, 0.02, n), W.rayleigh(r, 0.02, n)
+    node, peri = W.TWO_PI * r.random((2, n))
+    M = np.mod(r.uniform(0.0, 1.0, n) - node - peri, W.TWO_PI)
+    x, u = W.elements_to_cartesian(1.0 + m, a, e, inc, node, peri, M)
+    return m.reshape(nsys, npl), x.reshape(nsys, npl, 3), u.reshape(nsys, npl, 3)
 
 
 def _dev(a):
