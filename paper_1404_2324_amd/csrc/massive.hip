@@ -1981,56 +1981,121 @@ __global__ __launch_bounds__(256) void k_rcrit_init(
   chunk_tmax(t, i & ~63, tmax64);
 }
 
-// Per-body energy terms and angular momentum; rows[8 i + k]:
-// kinetic, -G m0 m/r, -1/2 G m sum_j m_j/r_ij, m v (3), m x x v (3) -> 9 terms
-__global__ void k_energy_rows(const double4* __restrict__ xm, const double4* __restrict__ vv,
-                              int n, double G, double m0, double* __restrict__ rows,
-                              const DevStat* __restrict__ st) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (i >= st->nlive) {  // padding rows (bodies that left) add nothing
-    for (int k = 0; k < 9; ++k) rows[9 * (size_t)i + k] = 0.0;
-    return;
-  }
-  const double4 p = xm[i], q = vv[i];
+// Energy and angular momentum (Eqs. 1-3), every pair once.  The bodies form T
+// tiles of 64 (T even: the padded count is a multiple of 256); tile ti pairs
+// with the tiles ti + d (mod T), d = 0 .. T/2, and d = 0 and d = T/2 count
+// half, since both of their tiles meet the other.  A wave holds the tile's
+// bodies one per lane and takes `per` offsets, its partners wave-uniform
+// through the scalar cache; a workgroup's sum of m_i m_j / r_ij is one number
+// in pot.  The offset-0 waves also leave their tile's eight other sums:
+// kinetic and star terms, m v (3), m x x v (3).
+// Bound: FP64 issue (12 instructions a pair) from a few thousand bodies on,
+// the launch below.  Splitting the pairs over the chip and taking each once,
+// where one lane per body walked every partner before: 2048 bodies 541 us ->
+// 11 us, 16384 bodies 4269 us -> 92 us; 16 bodies 4.8 us -> 4.9 us (rocprofv3,
+// this kernel; the sums after it take 5 us).
+constexpr int kEnW = 4;  // waves per workgroup
+constexpr int kEnU = 4;  // partners fetched ahead
+__global__ __launch_bounds__(kEnW * 64) void k_energy_part(const double4* __restrict__ xm,
+                                                           const double4* __restrict__ vv, int n,
+                                                           int T, int per, double G, double m0,
+                                                           double* __restrict__ pot,
+                                                           double* __restrict__ rows,
+                                                           const DevStat* __restrict__ st) {
+  __shared__ double sh[kEnW];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ti = blockIdx.x, i = ti * 64 + lane;
+  const double4 p = xm[i];
+  const bool act = i < st->nlive;  // padding rows (bodies that left) add nothing
+  const int d0 = (blockIdx.y * kEnW + wave) * per;
+  const int d1 = min(d0 + per, T / 2 + 1);
   double pp = 0.0;
-  for (int j = 0; j < n; ++j) {
-    if (j == i) continue;
-    const double4 pj = xm[j];
-    const double dx = pj.x - p.x, dy = pj.y - p.y, dz = pj.z - p.z;
-    pp += pj.w / sqrt(dx * dx + dy * dy + dz * dz);
+  for (int d = d0; d < d1; ++d) {
+    const int tj = ti + d >= T ? ti + d - T : ti + d;
+    const double4* xj = xm + tj * 64;
+    const int nj = min(64, n - tj * 64);  // padding rows past n add nothing
+    double4 cur[kEnU], nxt[kEnU];
+#pragma unroll
+    for (int u = 0; u < kEnU; ++u) nxt[u] = xj[u];
+    double s = 0.0;
+    for (int q0 = 0; q0 < nj; q0 += kEnU) {
+#pragma unroll
+      for (int u = 0; u < kEnU; ++u) cur[u] = nxt[u];
+      if (q0 + kEnU < nj) {
+#pragma unroll
+        for (int u = 0; u < kEnU; ++u) nxt[u] = xj[q0 + kEnU + u];
+      }
+#pragma unroll
+      for (int u = 0; u < kEnU; ++u) {
+        const double4 pj = cur[u];
+        const double dx = pj.x - p.x, dy = pj.y - p.y, dz = pj.z - p.z;
+        const double r2 = dx * dx + dy * dy + dz * dz;
+        const bool z = r2 == 0.0;
+        const double t = pj.w * rsqrt_nr(r2);
+        s += z ? 0.0 : t;
+        // a body against itself adds nothing; two bodies at one place do
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(z) != 0ull, 0))
+          if (z && tj * 64 + q0 + u != i) s += pj.w / sqrt(r2);
+      }
+    }
+    pp += (d == 0 || 2 * d == T) ? 0.5 * s : s;
   }
-  double* r = rows + 9 * (size_t)i;
-  r[0] = 0.5 * p.w * (q.x * q.x + q.y * q.y + q.z * q.z);
-  r[1] = -G * m0 * p.w / sqrt(p.x * p.x + p.y * p.y + p.z * p.z);
-  r[2] = -0.5 * G * p.w * pp;
-  r[3] = p.w * q.x;
-  r[4] = p.w * q.y;
-  r[5] = p.w * q.z;
-  r[6] = p.w * (p.y * q.z - p.z * q.y);
-  r[7] = p.w * (p.z * q.x - p.x * q.z);
-  r[8] = p.w * (p.x * q.y - p.y * q.x);
+  pp = wave_sum(act ? p.w * pp : 0.0);
+  if (lane == 0) sh[wave] = pp;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kEnW; ++w) t += sh[w];
+    pot[blockIdx.y * T + ti] = -G * t;
+  }
+  if (d0 != 0) return;
+  const double4 q = vv[i];
+  double r[8] = {0.5 * p.w * (q.x * q.x + q.y * q.y + q.z * q.z),
+                 -G * m0 * p.w / sqrt(p.x * p.x + p.y * p.y + p.z * p.z),
+                 p.w * q.x,
+                 p.w * q.y,
+                 p.w * q.z,
+                 p.w * (p.y * q.z - p.z * q.y),
+                 p.w * (p.z * q.x - p.x * q.z),
+                 p.w * (p.x * q.y - p.y * q.x)};
+#pragma unroll
+  for (int k = 0; k < 8; ++k) r[k] = wave_sum(act ? r[k] : 0.0);
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) rows[8 * ti + k] = r[k];
+  }
 }
 
-__global__ __launch_bounds__(256) void k_energy_final(const double* __restrict__ rows,
-                                                       int n, double m0,
-                                                       double* __restrict__ E,
-                                                       double* __restrict__ L) {
-  __shared__ double sh[16];
+// The tiles' and workgroups' sums added in a fixed order.
+__global__ __launch_bounds__(256) void k_energy_final(const double* __restrict__ pot, int npot,
+                                                      const double* __restrict__ rows, int T,
+                                                      double m0, double* __restrict__ E,
+                                                      double* __restrict__ L) {
+  __shared__ double sh[4][9];
   double t[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) t[k] = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256)
+  for (int i = threadIdx.x; i < T; i += 256)
 #pragma unroll
-    for (int k = 0; k < 9; ++k) t[k] += rows[9 * (size_t)i + k];
-  double s[9];
+    for (int k = 0; k < 8; ++k) t[k] += rows[8 * i + k];
+  for (int i = threadIdx.x; i < npot; i += 256) t[8] += pot[i];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) s[k] = block_sum<256>(t[k], sh);
+  for (int k = 0; k < 9; ++k) t[k] = wave_sum(t[k]);
+  if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) sh[threadIdx.x >> 6][k] = t[k];
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    E[0] = s[0] + (s[3] * s[3] + s[4] * s[4] + s[5] * s[5]) / (2.0 * m0) + s[1] + s[2];
-    L[0] = s[6];
-    L[1] = s[7];
-    L[2] = s[8];
+    double s[9];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) s[k] = ((sh[0][k] + sh[1][k]) + sh[2][k]) + sh[3][k];
+    E[0] = s[0] + (s[2] * s[2] + s[3] * s[3] + s[4] * s[4]) / (2.0 * m0) + s[1] + s[8];
+    L[0] = s[5];
+    L[1] = s[6];
+    L[2] = s[7];
   }
 }
 
@@ -2459,9 +2524,16 @@ hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
 
 hipError_t massive_energy(const MassiveWs& w, const StepConsts& c, double* dE,
                           double* dL, hipStream_t s) {
-  hipLaunchKernelGGL(k_energy_rows, dim3(ceil_div(w.n, 256)), dim3(256), 0, s, w.xs, w.vv,
-                     w.n, c.G, c.m0, w.red, (const DevStat*)w.st);
-  hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(256), 0, s, w.red, w.n, c.m0, dE, dL);
+  // one offset per wave up to 8192 waves, then longer walks
+  const int T = w.np / 64, D = T / 2 + 1;
+  const int per = std::max(1, T * D / 8192);
+  const int ny = ceil_div(D, kEnW * per);
+  double* rows = w.red;              // [T][8]
+  double* pot = w.red + 8 * (size_t)T;  // [ny][T]: 9 np doubles hold both
+  hipLaunchKernelGGL(k_energy_part, dim3(T, ny), dim3(kEnW * 64), 0, s, w.xs, w.vv, w.n, T, per, c.G,
+                     c.m0, pot, rows, (const DevStat*)w.st);
+  hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(256), 0, s, (const double*)pot, ny * T,
+                     (const double*)rows, T, c.m0, dE, dL);
   return hipGetLastError();
 }
 
