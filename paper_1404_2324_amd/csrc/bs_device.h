@@ -209,10 +209,9 @@ __device__ __forceinline__ int bs_integrate(int sz, int lane, double y[6], doubl
 // from the same start: exactly the attempts the sequential scheme makes
 // after s failures (the first half of each halving).  The Aitken-Neville
 // tableau is built across the columns (T[c][j] needs T[c-1][j-1]); column k
-// is tested when it completes (after 2 k + 3 force evaluations), and each
-// slot keeps its first column within tolerance.  The result is the first
-// accepted slot in sequential order, so the substeps taken equal those of
-// one-at-a-time evaluation.
+// is done after 2 k + 3 force evaluations.  The result is the first column
+// within tolerance of the first slot that has one, in sequential order, so the
+// substeps taken equal those of one-at-a-time evaluation.
 // TP: member 0 is a massless test particle and the other members feel only
 // the star (a test-particle encounter, Sec. 3.3).
 constexpr int kBsPar = 8;
@@ -234,6 +233,22 @@ template <int P>
 __device__ __forceinline__ unsigned long long par_members(int s, int c) {
   constexpr unsigned long long kStride = P == 2 ? 3ull : (P == 4 ? 0x01010101ull : 0x0101010101010101ull);
   return kStride << par_lane<P>(s, c, 0);
+}
+
+// Of a ballot over the lanes: the member-0 bits of the slots and columns whose
+// P members are all set, and of those the columns of slot s (bit c, or 2 c for
+// P = 2).
+template <int P>
+__device__ __forceinline__ unsigned long long par_all(unsigned long long m) {
+  if (P == 2) return m & (m >> 1) & 0x5555555555555555ull;
+  m &= m >> 8;
+  m &= m >> 16;
+  if (P == 8) return m & (m >> 32) & 0xFFull;
+  return m & 0x000000FF000000FFull;
+}
+template <int P>
+__device__ __forceinline__ unsigned par_cols(unsigned long long m, int s) {
+  return (unsigned)(m >> (kBsPar * P * s)) & (P == 2 ? 0xFFFFu : 0xFFu);
 }
 
 template <int P>
@@ -367,105 +382,126 @@ __device__ __forceinline__ bool within3(const double* A, const double* B, double
   return n2 <= tol2 * (a2 > 0.0 ? a2 : 1.0);
 }
 
+// Neville weights 1/((n_c/n_{c-j})^2 - 1) = (c-j+1)^2 / ((c+1)^2 - (c-j+1)^2) of
+// column c, j = 1 .. c, formed by the compiler (in a kernel they were 28
+// divisions before the first evaluation).
+struct BsWeights {
+  double w[kBsCols][kBsCols];
+};
+constexpr BsWeights bs_weights() {
+  BsWeights t{};
+  for (int c = 0; c < kBsCols; ++c)
+    for (int j = 1; j <= c; ++j) {
+      const int pp = c + 1, qq = c - j + 1;
+      t.w[c][j] = (double)(qq * qq) / (double)(pp * pp - qq * qq);
+    }
+  return t;
+}
+static __constant__ BsWeights kBsW = bs_weights();
+
+// Column that the first attempt of a group tests first; later ones start at
+// the column the last one accepted.
+constexpr int kBsFirstCol = 3;
+
 // One speculative round: returns the accepted depth offset (0..S-1), with the
-// accepted state in y, or -1 when every slot failed.
+// accepted state in y, or -1 when every slot failed.  hs: the lane's Gragg
+// substep (its column's, of its slot's depth); wj: its column's weights; mid:
+// the first column to test, set to the accepted one.
 template <int P, bool TP>
-__device__ __forceinline__ int bs_round_par(int sz, double y[6], double H,
-                                            const ParBody<P>& Q, double G,
-                                            double Gm0, double tol) {
+__device__ __forceinline__ int bs_round_par(int sz, double y[6], double hs,
+                                            const ParBody<P>& Q, double G, double Gm0, double tol,
+                                            const double (&wj)[kBsCols], int& mid) {
   const int lane = threadIdx.x & 63;
-  const int s = lane / (kBsPar * P);
   const int c = par_col<P>(lane);
   const int b = par_memb<P>(lane);
   const int nsub = 2 * (c + 1);
-  const double hs = ldexp(H, -s) / nsub;
   const double tol2 = tol >= 0.0 ? tol * tol : -1.0;  // a negative tolerance accepts nothing
   // Gragg states in two buffers used in turn: A holds the even-numbered
   // points z_0, z_2, ..., B the odd ones, so no copies are needed per substep
-  double A[6], B[6], T0[6], yacc[6];
+  double A[6], B[6];
 #pragma unroll
   for (int q = 0; q < 6; ++q) {
     A[q] = y[q];
     B[q] = y[q];
-    T0[q] = y[q];
-    yacc[q] = y[q];
   }
-  // Neville weights of this lane's column: 1/((n_c/n_{c-j})^2 - 1) =
-  // (c-j+1)^2 / ((c+1)^2 - (c-j+1)^2), j = 1..c
-  double wj[kBsCols];
-#pragma unroll
-  for (int j = 1; j < kBsCols; ++j) {
-    const int pp = c + 1, qq = c - j + 1;
-    wj[j] = j <= c ? (double)(qq * qq) / (double)(pp * pp - qq * qq) : 0.0;
-  }
-  unsigned accm = 0u;  // slots that have accepted a column (bit s)
   // Evaluation e is at z_e: z_1 = z_0 + hs f(z_0), z_{e+1} = z_{e-1} +
   // 2 hs f(z_e) while e < nsub; the lane's points stay fixed after z_nsub
-  // (step 0), and T0 = (z_{nsub-1} + z_nsub + hs f(z_nsub)) / 2.
-  for (int e = 0; e <= 2 * kBsCols; e += 2) {
+  // (step 0), so at any later even e the lane still evaluates f(z_nsub) and
+  // T[c][0] = (z_{nsub-1} + z_nsub + hs f(z_nsub)) / 2 can be formed there.
+  // The columns are tested together when column mid is done, then at mid + 1
+  // and at the last: a test costs 1000 cycles where an evaluation of a pair
+  // costs 353 (one wave on its SIMD, bound by FP64 issue), and an attempt
+  // mostly accepts near the column the one before it did.  Which columns are
+  // tested when does not change the result.  An attempt of a pair that stops
+  // at column 4 took 7980 cycles with a test per column, 5840 with one there;
+  // the refinement kernel of 10^6 test particles 154 us -> 134 us a step.
+  for (int e = 0;; e += 2) {
     double d[6];
     ha_accel_par<P, TP>(sz, b, A[0], A[1], A[2], Q, G, Gm0, d[3], d[4], d[5]);
     d[0] = A[3];
     d[1] = A[4];
     d[2] = A[5];
-    if (e == nsub) {
+    const int k = e / 2 - 1;  // column completed by this evaluation
+    if (k == mid || k == mid + 1 || k == kBsCols - 1) {
+      // Aitken-Neville across the columns: T[c][j] needs T[c-1][j-1] (lane
+      // - 1 or - 2 of the row): after j steps lane c <= k holds T[c][min(j,
+      // c)], so every column up to k ends with its diagonal in cur and
+      // T[c][c-1] in sub.  Columns past k hold values that no lane <= k reads.
+      double cur[6], sub[6];
 #pragma unroll
-      for (int q = 0; q < 6; ++q) T0[q] = 0.5 * (B[q] + A[q] + hs * d[q]);
+      for (int q = 0; q < 6; ++q) {
+        cur[q] = 0.5 * (B[q] + A[q] + hs * d[q]);
+        sub[q] = cur[q];
+      }
+#pragma unroll
+      for (int j = 1; j < kBsCols; ++j) {
+        if (j > k) break;
+        double nb[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+          nb[q] = P == 2 ? dpp_d<kDppRowShr2>(cur[q]) : dpp_d<kDppRowShr1>(cur[q]);
+        if (c >= j) {
+          const double w = wj[j];
+#pragma unroll
+          for (int q = 0; q < 6; ++q) {
+            sub[q] = cur[q];
+            cur[q] = fma(cur[q] - nb[q], w, cur[q]);
+          }
+        }
+      }
+      // lanes of the columns 1 .. k whose member is within tolerance
+      const bool good = c >= 1 && c <= k &&
+                        (b >= sz || (within3(cur, sub, tol2) && within3(cur + 3, sub + 3, tol2)));
+      const unsigned long long gm = par_all<P>(__ballot(good));
+      // slot 0 decided: nothing can precede it; else the first accepted slot
+      // in sequential order once every column is done
+      unsigned cols = par_cols<P>(gm, 0);
+      int sacc = 0;
+      if (cols == 0u && k == kBsCols - 1) {
+#pragma unroll
+        for (int t = kBsPar / P - 1; t >= 1; --t) {
+          const unsigned ct = par_cols<P>(gm, t);
+          if (ct) {
+            cols = ct;
+            sacc = t;
+          }
+        }
+        if (cols == 0u) return -1;
+      }
+      if (cols) {
+        // the slot's first accepted column (bit kc, or 2 kc for P = 2)
+        const int kc = P == 2 ? (__ffs(cols) - 1) >> 1 : __ffs(cols) - 1;
+#pragma unroll
+        for (int q = 0; q < 6; ++q) y[q] = shfl_d(cur[q], par_lane<P>(sacc, kc, b));
+        mid = kc;
+        return sacc;
+      }
     }
     {
       const double hf = e < nsub ? (e == 0 ? hs : 2.0 * hs) : 0.0;
 #pragma unroll
       for (int q = 0; q < 6; ++q) B[q] = B[q] + hf * d[q];
     }
-    if (e >= 4) {
-      const int k = e / 2 - 1;  // column completed by this evaluation
-      // Aitken-Neville across the columns: T[c][j] needs T[c-1][j-1] (lane - P).
-      // Only column k's lanes are read: after j steps lane k holds T[k][j],
-      // built from lane k-1 after j-1 steps, ..., lane k-j's T0, all of
-      // them inside their own row (j <= c).  Lanes past their row (w = 0)
-      // keep computing, and whatever they hold never reaches lane k.
-      double cur[6], sub[6];
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
-        cur[q] = T0[q];
-        sub[q] = T0[q];
-      }
-#pragma unroll
-      for (int j = 1; j < kBsCols; ++j) {
-        if (j > k) break;
-        if (j == k) {
-#pragma unroll
-          for (int q = 0; q < 6; ++q) sub[q] = cur[q];  // T[k][k-1] in lane k
-        }
-        const double w = wj[j];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-          const double nb = P == 2 ? dpp_d<kDppRowShr2>(cur[q]) : dpp_d<kDppRowShr1>(cur[q]);
-          cur[q] = fma(cur[q] - nb, w, cur[q]);
-        }
-      }
-      const double* diag = cur;  // T[k][k] in lane k
-      // column k of every slot: accepted unless one of its members fails
-      const bool bad = c == k && b < sz && !(within3(diag, sub, tol2) && within3(diag + 3, sub + 3, tol2));
-      const unsigned long long badm = __ballot(bad);
-      unsigned now = 0u;
-#pragma unroll
-      for (int t = 0; t < kBsPar / P; ++t)
-        if (!((accm >> t) & 1u) && (badm & par_members<P>(t, k)) == 0ull)
-          now |= 1u << t;
-      if (now) {
-        // the accepted state of this slot's column k, for every lane of the slot
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-          const double g = shfl_d(diag[q], par_lane<P>(s, k, b));
-          if ((now >> s) & 1u) yacc[q] = g;
-        }
-        accm |= now;
-      }
-      // slot 0 decided: nothing can precede it
-      if (accm & 1u) break;
-    }
-    if (e == 2 * kBsCols) break;
     ha_accel_par<P, TP>(sz, b, B[0], B[1], B[2], Q, G, Gm0, d[3], d[4], d[5]);
     d[0] = B[3];
     d[1] = B[4];
@@ -474,12 +510,6 @@ __device__ __forceinline__ int bs_round_par(int sz, double y[6], double H,
 #pragma unroll
     for (int q = 0; q < 6; ++q) A[q] = A[q] + hf * d[q];
   }
-  // first accepted slot in sequential order
-  if (accm == 0u) return -1;
-  const int sacc = __ffs(accm) - 1;
-#pragma unroll
-  for (int q = 0; q < 6; ++q) y[q] = shfl_d(yacc[q], par_lane<P>(sacc, 0, b));
-  return sacc;
 }
 
 // Test-particle groups (TP) with R2 >= 0 in some lane: after each accepted
@@ -494,15 +524,21 @@ __device__ __forceinline__ int bs_round_par(int sz, double y[6], double H,
 // a * 64 + b in *cb.
 template <int P, bool TP>
 __device__ __forceinline__ int bs_integrate_par(int sz, double y[6], double H,
-                                                const ParBody<P>& Q, double G,
-                                                double Gm0, double tol, int D,
-                                                long long* nsub, double R2 = -1.0,
+                                                const ParBody<P>& Q, double G, double Gm0,
+                                                double tol, int D, long long* nsub, double R2 = -1.0,
                                                 int* cb = nullptr,
                                                 long long* cpos = nullptr,
                                                 const double* mR = nullptr) {
   constexpr int S = kBsPar / P;
   const int lane = threadIdx.x & 63;
   const int b = par_memb<P>(lane);
+  const int c8 = par_col<P>(lane), s8 = lane / (kBsPar * P);
+  // the substeps of every depth are this one scaled by a power of two (exact)
+  const double hn = H / (2 * (c8 + 1));
+  double wj[kBsCols];
+#pragma unroll
+  for (int j = 1; j < kBsCols; ++j) wj[j] = kBsW.w[c8][j];
+  int mid = kBsFirstCol;
   const bool coll = TP && __ballot(R2 >= 0.0) != 0ull;
   const double Rb = (!TP && mR && b < sz) ? mR[b] : 0.0;
   const bool mcoll = !TP && mR && __ballot(Rb > 0.0) != 0ull;
@@ -516,7 +552,7 @@ __device__ __forceinline__ int bs_integrate_par(int sz, double y[6], double H,
     double yt[6];
 #pragma unroll
     for (int q = 0; q < 6; ++q) yt[q] = y[q];
-    int sa = bs_round_par<P, TP>(sz, yt, ldexp(H, -d), Q, G, Gm0, tol);
+    int sa = bs_round_par<P, TP>(sz, yt, ldexp(hn, -(d + s8)), Q, G, Gm0, tol, wj, mid);
     if (sa >= smax) sa = -1;
     if (sa >= 0) {
       d += sa;
@@ -592,7 +628,11 @@ __device__ __forceinline__ ParBody<P> par_body(int sz, const double* mm, const d
     j = j >= sz ? j - sz : j;
     j = j >= sz ? j - sz : j;  // dummy slots (b >= sz) wrap twice at most
     Q.lane[q] = lane + par_lane<P>(0, 0, j) - par_lane<P>(0, 0, b);
-    const int jb = ((b - q) % sz + sz) % sz;  // member (b - q) mod sz (dummies too)
+    // member (b - q) mod sz, with P < 2 sz or sz = 1 (dummies too)
+    int jb = b - q;
+    jb = jb < 0 ? jb + sz : jb;
+    jb = jb < 0 ? (sz > 1 ? jb + sz : 0) : jb;
+    jb = jb >= sz ? (sz > 1 ? jb - sz : 0) : jb;
     Q.lback[q] = lane + par_lane<P>(0, 0, jb) - par_lane<P>(0, 0, b);
     Q.mback[q] = q < sz ? mm[jb] : 0.0;
     Q.m[q] = 0.0;

@@ -1235,10 +1235,11 @@ __device__ int bs_group_big(const BsArgs& a, const int* gm, int o, int sz, long 
   return status;
 }
 
-// Depth-slot exchange of the waves integrating one group.
+// Depth-slot exchange of the waves integrating one group, used in turn by the
+// rounds (a wave enters round r + 2 only after every wave has read round r).
 struct BsXchg {
-  int gs[kBsWaves];         // each wave's first accepted slot (INT_MAX: none)
-  double y[kBsPar][6];      // the winning slot's state per member
+  int gs[2][kBsWaves];                // each wave's first accepted slot (INT_MAX: none)
+  double y[2][kBsWaves][kBsPar][6];   // its state per member
 };
 
 // Binary refinement over [0, H] of a group of sz <= P members by the
@@ -1246,7 +1247,8 @@ struct BsXchg {
 // d + w S .. d + w S + S - 1 (S = kBsPar / P per wave, as bs_round_par lays
 // them out), so that kBsWaves S halvings of the substep are attempted at
 // once from the same start.  The first accepted slot in sequential order
-// wins; its state reaches every wave through LDS, and the waves, holding the
+// wins; its state reaches every wave through LDS (each wave writes its own
+// beside its slot, so one barrier serves a round), and the waves, holding the
 // same state, position and depth, go on together.  The substeps taken and
 // their results are those of the one-wave bs_integrate_par.
 template <int P>
@@ -1257,33 +1259,43 @@ __device__ __forceinline__ int bs_integrate_mw(int sz, double y[6], double H,
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int b = par_memb<P>(lane);
+  const int c = par_col<P>(lane), s = wave * S + lane / (kBsPar * P);
+  // the substeps of every depth are this one scaled by a power of two (exact)
+  const double hn = H / (2 * (c + 1));
+  double wj[kBsCols];
+#pragma unroll
+  for (int j = 1; j < kBsCols; ++j) wj[j] = kBsW.w[c][j];
+  int mid = kBsFirstCol;
   long long pos = 0;
   const long long total = 1ll << D;
   int d = 0, attempts = 0;
   while (pos < total) {
     if (++attempts > kBsMaxAttempts) return -1;
     const int smax = min(kBsWaves * S, D - d + 1);  // never beyond the depth limit
+    const int buf = attempts & 1;
     double yt[6];
 #pragma unroll
     for (int q = 0; q < 6; ++q) yt[q] = y[q];
     int gs = INT_MAX;
     if (wave * S < smax) {
-      const int sa = bs_round_par<P, false>(sz, yt, ldexp(H, -(d + wave * S)), Q, G, Gm0, tol);
-      if (sa >= 0 && wave * S + sa < smax) gs = wave * S + sa;
-    }
-    if (lane == 0) X.gs[wave] = gs;
-    __syncthreads();
-    int best = X.gs[0];
+      const int sa = bs_round_par<P, false>(sz, yt, ldexp(hn, -(d + s)), Q, G, Gm0, tol, wj, mid);
+      if (sa >= 0 && wave * S + sa < smax) {
+        gs = wave * S + sa;
+        if (lane == par_lane<P>(0, 0, b)) {
 #pragma unroll
-    for (int w = 1; w < kBsWaves; ++w) best = min(best, X.gs[w]);
-    if (best != INT_MAX) {
-      if (wave == best / S && lane == par_lane<P>(0, 0, b)) {
-#pragma unroll
-        for (int q = 0; q < 6; ++q) X.y[b][q] = yt[q];
+          for (int q = 0; q < 6; ++q) X.y[buf][wave][b][q] = yt[q];
+        }
       }
-      __syncthreads();
+    }
+    if (lane == 0) X.gs[buf][wave] = gs;
+    __syncthreads();
+    int best = X.gs[buf][0];
 #pragma unroll
-      for (int q = 0; q < 6; ++q) y[q] = X.y[b][q];
+    for (int w = 1; w < kBsWaves; ++w) best = min(best, X.gs[buf][w]);
+    best = __builtin_amdgcn_readfirstlane(best);
+    if (best != INT_MAX) {
+#pragma unroll
+      for (int q = 0; q < 6; ++q) y[q] = X.y[buf][best / S][b][q];
       d += best;
       ++*nsub;
       pos += 1ll << (D - d);
@@ -1291,8 +1303,6 @@ __device__ __forceinline__ int bs_integrate_mw(int sz, double y[6], double H,
     } else {
       d += smax;
     }
-    // X is written again only after every wave has read it
-    __syncthreads();
     if (d > D) return -1;
   }
   return 0;
