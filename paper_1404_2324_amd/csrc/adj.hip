@@ -14,11 +14,19 @@
 //          functions of r0 = |x|, eta0 = x.v, beta = 2 mu/r0 - v^2 and the
 //          universal anomaly s, which solves r0 G1 + eta0 G2 + mu G3 = tau
 //          (implicit function: ds/dq = -(dF/dq)/r).
-// Systems are packed SB (a power of two >= the largest system) lanes each,
-// 64/SB systems per wave; pair terms move by lane shuffles inside a segment.
+// Layout.  A body has PL lanes (a power of two) and a system SB bodies' worth
+// of them, SB the power of two not below the largest system: lane PL b + p
+// holds a copy of body b and takes the pair terms with the partners p, p + PL,
+// ..., summed over p by DPP.  The map is a serial chain per system, so while
+// the systems leave the chip idle PL = min(SB, 64 / SB) shortens the chain: 1024
+// systems of 8 are 1024 waves (one per SIMD) with one pair term per lane and
+// kick, where PL = 1 gives 128 waves with eight (250 steps: forward 990 us -> 417
+// us, backward 2190 us -> 894 us with the tape below).  With enough systems the
+// copies only repeat work, and PL = 1 (64 / SB systems per wave) is used.
 #include <algorithm>
 
 #include "adj_device.h"
+#include "bs_device.h"
 #include "device_math.h"
 #include "genga_impl.h"
 
@@ -31,32 +39,47 @@ struct AdjArgs {
   const int* __restrict__ off;
   const double* __restrict__ m0;
   double* __restrict__ ckpt;      // [C][6][nb]
-  double* __restrict__ tape;      // [k][6][nlanes]
+  double* __restrict__ tape;      // [k][7][nb]: pre-drift x, v and universal anomaly
   const double* __restrict__ gxT;  // [nb][3]
   const double* __restrict__ gvT;
   double* __restrict__ gx0;
   double* __restrict__ gv0;
   double* __restrict__ gm;        // [nb]
   unsigned* __restrict__ flags;
-  int nsys, T, K, C, nlanes;
+  int nsys, T, K, C;
   int64_t nb;
   double G, dt, h, n1, n2, absdt;
   int max_iter;
 };
 
-template <int SB>
+template <int SB, int PL>
 struct Lane {
-  int seg, b, s, row, n;
+  static constexpr int LS = SB * PL;  // lanes of a system
+  static constexpr int NT = SB / PL;  // partners a lane takes
+  static constexpr bool KEEP = NT <= 8;  // the partners' masses stay in registers
+  static constexpr int UNROLL = KEEP ? NT : 4;
+  int base, b, p, s, row, n;
   bool act;
+  double m, m0, Gm0, iGm0;
+  double mj[KEEP ? NT : 1];  // their masses, 0 for the lane's own body
+  __device__ __forceinline__ int src(int t) const { return base + PL * (p + PL * t); }
+  __device__ __forceinline__ bool own(int t) const { return p + PL * t == b; }
+  __device__ __forceinline__ double mass(int t) const {
+    if (KEEP) return mj[KEEP ? t : 0];
+    const double q = shfl_d(m, src(t));
+    return own(t) ? 0.0 : q;
+  }
 };
 
-template <int SB>
-__device__ __forceinline__ Lane<SB> lane_of(const AdjArgs& a) {
-  Lane<SB> L;
+template <int SB, int PL>
+__device__ __forceinline__ Lane<SB, PL> lane_of(const AdjArgs& a) {
+  using LT = Lane<SB, PL>;
+  LT L;
   const int lane = threadIdx.x & 63;
-  L.seg = lane / SB;
-  L.b = lane % SB;
-  L.s = blockIdx.x * (64 / SB) + L.seg;
+  L.base = lane & ~(LT::LS - 1);
+  L.b = (lane - L.base) / PL;
+  L.p = lane & (PL - 1);
+  L.s = blockIdx.x * (64 / LT::LS) + lane / LT::LS;
   L.n = 0;
   L.row = 0;
   if (L.s < a.nsys) {
@@ -64,118 +87,152 @@ __device__ __forceinline__ Lane<SB> lane_of(const AdjArgs& a) {
     L.row = a.off[L.s] + L.b;
   }
   L.act = L.b < L.n;
+  L.m0 = L.s < a.nsys ? a.m0[L.s] : 1.0;
+  L.Gm0 = a.G * L.m0;
+  L.iGm0 = 1.0 / L.Gm0;
+  L.m = L.act ? a.xm[L.row].w : 0.0;
+  if (LT::KEEP) {
+#pragma unroll
+    for (int t = 0; t < LT::NT; ++t) {
+      const double q = shfl_d(L.m, L.src(t));
+      L.mj[t] = L.own(t) ? 0.0 : q;
+    }
+  }
   return L;
 }
 
-template <int SB>
-__device__ __forceinline__ double seg_sum(double v) {
-#pragma unroll
-  for (int o = SB / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// v plus its partner's at lane distance D; the values are uniform over the D
+// lanes around (copies, or sums over the smaller distances), so the mirrors
+// and row swaps pair them as lane ^ D would.
+template <int D>
+__device__ __forceinline__ double xor_add(double v) {
+  if (D == 1) return v + dpp_d<kDppQuadSwap1>(v);
+  if (D == 2) return v + dpp_d<kDppQuadSwap2>(v);
+  if (D == 4) return v + dpp_d<kDppRowHalfMirror>(v);
+  if (D == 8) return v + dpp_d<kDppRowMirror>(v);
+  return swap_sum<D == 32 ? 32 : 16>(v);
+}
+
+// Sum over the lane distances D, 2 D, ..., below E.
+template <int D, int E>
+__device__ __forceinline__ double dist_sum(double v) {
+  if constexpr (D < E) return dist_sum<2 * D, E>(xor_add<D>(v));
   return v;
 }
 
-// a_i = sum_j G m_j (x_j - x_i)/r^3 inside the lane's segment.
-template <int SB>
-__device__ __forceinline__ void seg_acc(double G, double x, double y, double z, double m,
-                                        double& ax, double& ay, double& az) {
-  const int lane = threadIdx.x & 63, base = lane & ~(SB - 1);
-  ax = ay = az = 0.0;
-#pragma unroll 4
-  for (int j = 0; j < SB; ++j) {
-    const double xj = __shfl(x, base + j, 64), yj = __shfl(y, base + j, 64),
-                 zj = __shfl(z, base + j, 64), mj = __shfl(m, base + j, 64);
-    if (base + j != lane) {
-      const double dx = xj - x, dy = yj - y, dz = zj - z;
-      const double ir = rsqrt_nr(dx * dx + dy * dy + dz * dz);
-      const double s = mj * ir * ir * ir;
-      ax += s * dx;
-      ay += s * dy;
-      az += s * dz;
-    }
-  }
-  ax *= G;
-  ay *= G;
-  az *= G;
+// Over the partner lanes of a body; over the bodies of the system (one copy
+// of each).
+template <int SB, int PL>
+__device__ __forceinline__ double part_sum(double v) {
+  return dist_sum<1, PL>(v);
+}
+template <int SB, int PL>
+__device__ __forceinline__ double seg_sum(double v) {
+  return dist_sum<PL, SB * PL>(v);
 }
 
-// One step of the encounter-free map.
-template <int SB>
-__device__ __forceinline__ void free_step(const AdjArgs& a, bool act, double Gm0, double m0,
-                                          double m, double& x, double& y, double& z, double& vx,
-                                          double& vy, double& vz, unsigned& fl) {
-  double ax, ay, az;
-  seg_acc<SB>(a.G, x, y, z, m, ax, ay, az);
-  vx += a.h * ax;
-  vy += a.h * ay;
-  vz += a.h * az;
-  const double hm0 = a.h / m0;  // the Sun kick's factor (the replay uses the same)
-  double Px = seg_sum<SB>(m * vx), Py = seg_sum<SB>(m * vy), Pz = seg_sum<SB>(m * vz);
-  x += hm0 * Px;
-  y += hm0 * Py;
-  z += hm0 * Pz;
-  if (act && kepler_drift(Gm0, a.dt, x, y, z, vx, vy, vz, a.max_iter) < 0) fl |= F_KEPLER;
-  Px = seg_sum<SB>(m * vx);
-  Py = seg_sum<SB>(m * vy);
-  Pz = seg_sum<SB>(m * vz);
-  x += hm0 * Px;
-  y += hm0 * Py;
-  z += hm0 * Pz;
-  seg_acc<SB>(a.G, x, y, z, m, ax, ay, az);
-  vx += a.h * ax;
-  vy += a.h * ay;
-  vz += a.h * az;
-}
-
-// A pair inside r_crit (Eq. 6) means the hybrid method would switch the pair
-// to K < 1 there, so the K = 1 map is no longer the method's step.
-template <int SB>
-__device__ __forceinline__ bool seg_close(const AdjArgs& a, bool act, double Gm0, double m0,
-                                          double m, double x, double y, double z, double vx,
-                                          double vy, double vz) {
-  const int lane = threadIdx.x & 63, base = lane & ~(SB - 1);
-  const double rc = act ? rcrit(x, y, z, vx, vy, vz, m, Gm0, m0, a.n1, a.n2, a.absdt) : 0.0;
+// a_i = sum_j G m_j (x_j - x_i)/r^3 over the system.  With rc2 >= 0 (the
+// squared critical radius; the start of a step) also whether some massive
+// partner of the lane is inside it or inside its own.
+template <int SB, int PL, bool CLOSE>
+__device__ __forceinline__ bool seg_acc(double G, const Lane<SB, PL>& L, double x, double y,
+                                        double z, double rc2, double& ax, double& ay,
+                                        double& az) {
   bool close = false;
-  for (int j = 0; j < SB; ++j) {
-    const double xj = __shfl(x, base + j, 64), yj = __shfl(y, base + j, 64),
-                 zj = __shfl(z, base + j, 64), rcj = __shfl(rc, base + j, 64);
-    const double mj = __shfl(m, base + j, 64);
-    if (act && mj > 0.0 && base + j != lane) {
-      const double dx = xj - x, dy = yj - y, dz = zj - z;
-      const double rcij = fmax(rc, rcj);
-      if (dx * dx + dy * dy + dz * dz < rcij * rcij) close = true;
-    }
+  ax = ay = az = 0.0;
+  constexpr int U = Lane<SB, PL>::UNROLL;
+#pragma unroll U
+  for (int t = 0; t < Lane<SB, PL>::NT; ++t) {
+    const int l = L.src(t);
+    const double dx = shfl_d(x, l) - x, dy = shfl_d(y, l) - y, dz = shfl_d(z, l) - z;
+    const double mj = L.mass(t);
+    const double d2 = dx * dx + dy * dy + dz * dz;
+    const double ir = rsqrt_nr(L.own(t) ? 1.0 : d2);
+    const double s = mj * ir * ir * ir;
+    ax += s * dx;
+    ay += s * dy;
+    az += s * dz;
+    if (CLOSE) close = close || (mj > 0.0 && d2 < fmax(rc2, shfl_d(rc2, l)));
   }
+  ax = G * part_sum<SB, PL>(ax);
+  ay = G * part_sum<SB, PL>(ay);
+  az = G * part_sum<SB, PL>(az);
   return close;
 }
 
-template <int SB>
-__device__ __forceinline__ void load_state(const AdjArgs& a, const Lane<SB>& L, double& x,
-                                           double& y, double& z, double& vx, double& vy,
-                                           double& vz, double& m) {
-  const int lane = threadIdx.x & 63;
-  x = 1.0e3 + lane;  // inactive lanes: massless, far away
-  y = z = vx = vy = vz = m = 0.0;
+// One step of the encounter-free map; x2, v1 and sK receive the state the
+// drift starts from and its universal anomaly.
+template <int SB, int PL, bool CLOSE>
+__device__ __forceinline__ void free_step(const AdjArgs& a, const Lane<SB, PL>& L, double cb,
+                                          double& x, double& y, double& z, double& vx,
+                                          double& vy, double& vz, double x2[3], double v1[3],
+                                          double& sK, unsigned& fl) {
+  double ax, ay, az, rc2 = 0.0;
+  if (CLOSE) {
+    // Eq. (6), squared; n1 (m / 3 m0)^(1/3) is the lane's constant cb
+    const double r2 = x * x + y * y + z * z, vv = vx * vx + vy * vy + vz * vz;
+    const double ir = rsqrt_nr(r2);
+    const double inva = 2.0 * ir - vv * L.iGm0;
+    const double q = cb * (inva > 0.0 ? rcp_nr(inva) : r2 * ir), w = a.n2 * a.absdt;
+    rc2 = L.act ? fmax(q * q, w * w * vv) : 0.0;
+  }
+  // A pair inside r_crit (Eq. 6) means the hybrid method would switch the pair
+  // to K < 1 there, so the K = 1 map is no longer the method's step.
+  if (seg_acc<SB, PL, CLOSE>(a.G, L, x, y, z, rc2, ax, ay, az) && L.act) fl |= F_ADJ_ENC;
+  vx += a.h * ax;
+  vy += a.h * ay;
+  vz += a.h * az;
+  const double hm0 = a.h / L.m0;  // the Sun kick's factor (the replay uses the same)
+  double Px = seg_sum<SB, PL>(L.m * vx), Py = seg_sum<SB, PL>(L.m * vy),
+         Pz = seg_sum<SB, PL>(L.m * vz);
+  x += hm0 * Px;
+  y += hm0 * Py;
+  z += hm0 * Pz;
+  x2[0] = x;
+  x2[1] = y;
+  x2[2] = z;
+  v1[0] = vx;
+  v1[1] = vy;
+  v1[2] = vz;
+  sK = 0.0;
+  if (L.act && kepler_drift(L.Gm0, a.dt, x, y, z, vx, vy, vz, a.max_iter, &sK) < 0)
+    fl |= F_KEPLER;
+  Px = seg_sum<SB, PL>(L.m * vx);
+  Py = seg_sum<SB, PL>(L.m * vy);
+  Pz = seg_sum<SB, PL>(L.m * vz);
+  x += hm0 * Px;
+  y += hm0 * Py;
+  z += hm0 * Pz;
+  seg_acc<SB, PL, false>(a.G, L, x, y, z, 0.0, ax, ay, az);
+  vx += a.h * ax;
+  vy += a.h * ay;
+  vz += a.h * az;
+}
+
+// Inactive lanes: massless, far away and apart.
+template <int SB, int PL>
+__device__ __forceinline__ double far_x(const Lane<SB, PL>& L) {
+  return 1.0e3 + L.base + L.b;
+}
+
+template <int SB, int PL>
+__global__ __launch_bounds__(64) void k_adj_fwd(AdjArgs a) {
+  const Lane<SB, PL> L = lane_of<SB, PL>(a);
+  double x = far_x(L), y = 0.0, z = 0.0, vx = 0.0, vy = 0.0, vz = 0.0;
   if (L.act) {
     const double4 p = a.xm[L.row], q = a.vv[L.row];
     x = p.x;
     y = p.y;
     z = p.z;
-    m = p.w;
     vx = q.x;
     vy = q.y;
     vz = q.z;
   }
-}
-
-template <int SB>
-__global__ __launch_bounds__(64) void k_adj_fwd(AdjArgs a) {
-  const Lane<SB> L = lane_of<SB>(a);
-  double x, y, z, vx, vy, vz, m;
-  load_state<SB>(a, L, x, y, z, vx, vy, vz, m);
-  const double m0 = L.s < a.nsys ? a.m0[L.s] : 1.0, Gm0 = a.G * m0;
+  const double cb = a.n1 * cbrt(L.m / (3.0 * L.m0));
+  const bool wr = L.act && L.p == 0;  // one lane of each body writes
   unsigned fl = 0u;
   for (int t = 0; t < a.T; ++t) {
-    if (t % a.K == 0 && L.act) {
+    if (t % a.K == 0 && wr) {
       double* c = a.ckpt + (size_t)(t / a.K) * 6 * a.nb;
       c[L.row] = x;
       c[a.nb + L.row] = y;
@@ -184,11 +241,11 @@ __global__ __launch_bounds__(64) void k_adj_fwd(AdjArgs a) {
       c[4 * a.nb + L.row] = vy;
       c[5 * a.nb + L.row] = vz;
     }
-    if (seg_close<SB>(a, L.act, Gm0, m0, m, x, y, z, vx, vy, vz)) fl |= F_ADJ_ENC;
-    free_step<SB>(a, L.act, Gm0, m0, m, x, y, z, vx, vy, vz, fl);
+    double x2[3], v1[3], sK;
+    free_step<SB, PL, true>(a, L, cb, x, y, z, vx, vy, vz, x2, v1, sK, fl);
   }
-  if (L.act) {
-    a.xm[L.row] = make_double4(x, y, z, m);
+  if (wr) {
+    a.xm[L.row] = make_double4(x, y, z, L.m);
     a.vv[L.row] = make_double4(vx, vy, vz, 0.0);
   }
   if (fl) atomicOr(a.flags, fl);
@@ -197,45 +254,44 @@ __global__ __launch_bounds__(64) void k_adj_fwd(AdjArgs a) {
 // ---- vector-Jacobian products ----------------------------------------------
 // (J_a^T w)_k = sum_j T_kj (m_k w_j - m_j w_k), T = G (I/r^3 - 3 d d^T/r^5),
 // and (da/dm)^T w for m_k = sum_i G (x_k - x_i).w_i / r_ik^3.
-template <int SB>
-__device__ __forceinline__ void kick_vjp(double G, double h, double x, double y, double z,
-                                         double m, double wx, double wy, double wz,
+template <int SB, int PL>
+__device__ __forceinline__ void kick_vjp(double G, double h, const Lane<SB, PL>& L, double x,
+                                         double y, double z, double wx, double wy, double wz,
                                          double& gx, double& gy, double& gz, double& gmass) {
-  const int lane = threadIdx.x & 63, base = lane & ~(SB - 1);
   double sx = 0.0, sy = 0.0, sz = 0.0, sm = 0.0;
-#pragma unroll 2
-  for (int j = 0; j < SB; ++j) {
-    const int l = base + j;
-    const double xj = __shfl(x, l, 64), yj = __shfl(y, l, 64), zj = __shfl(z, l, 64);
-    const double mj = __shfl(m, l, 64);
-    const double wxj = __shfl(wx, l, 64), wyj = __shfl(wy, l, 64), wzj = __shfl(wz, l, 64);
-    if (l != lane) {
-      const double dx = xj - x, dy = yj - y, dz = zj - z;
-      const double ir = rsqrt_nr(dx * dx + dy * dy + dz * dz);
-      const double ir2 = ir * ir, ir3 = ir2 * ir;
-      // u = m_k w_j - m_j w_k;  T u = u/r^3 - 3 d (d.u)/r^5
-      const double ux = m * wxj - mj * wx, uy = m * wyj - mj * wy, uz = m * wzj - mj * wz;
-      const double du = 3.0 * (dx * ux + dy * uy + dz * uz) * ir3 * ir2;
-      sx += ux * ir3 - dx * du;
-      sy += uy * ir3 - dy * du;
-      sz += uz * ir3 - dz * du;
-      // d = x_j - x_k, so (x_k - x_j).w_j = -d.w_j
-      sm -= (dx * wxj + dy * wyj + dz * wzj) * ir3;
-    }
+  constexpr int U = Lane<SB, PL>::UNROLL;
+#pragma unroll U
+  for (int t = 0; t < Lane<SB, PL>::NT; ++t) {
+    const int l = L.src(t);
+    const double dx = shfl_d(x, l) - x, dy = shfl_d(y, l) - y, dz = shfl_d(z, l) - z;
+    const double wxj = shfl_d(wx, l), wyj = shfl_d(wy, l), wzj = shfl_d(wz, l);
+    const double mj = L.mass(t);
+    const bool own = L.own(t);  // its terms are exact zeros below: d = 0, and u is not used
+    const double ir = rsqrt_nr(own ? 1.0 : dx * dx + dy * dy + dz * dz);
+    const double ir2 = ir * ir, ir3 = own ? 0.0 : ir2 * ir;
+    // u = m_k w_j - m_j w_k;  T u = u/r^3 - 3 d (d.u)/r^5
+    const double ux = L.m * wxj - mj * wx, uy = L.m * wyj - mj * wy, uz = L.m * wzj - mj * wz;
+    const double du = 3.0 * (dx * ux + dy * uy + dz * uz) * ir3 * ir2;
+    sx += ux * ir3 - dx * du;
+    sy += uy * ir3 - dy * du;
+    sz += uz * ir3 - dz * du;
+    // d = x_j - x_k, so (x_k - x_j).w_j = -d.w_j
+    sm -= (dx * wxj + dy * wyj + dz * wzj) * ir3;
   }
-  gx += h * G * sx;
-  gy += h * G * sy;
-  gz += h * G * sz;
-  gmass += h * G * sm;
+  const double hG = h * G;
+  gx += hG * part_sum<SB, PL>(sx);
+  gy += hG * part_sum<SB, PL>(sy);
+  gz += hG * part_sum<SB, PL>(sz);
+  gmass += hG * part_sum<SB, PL>(sm);
 }
 
-template <int SB>
+// A step's reverse reads its drift's start (x2, v1) and universal anomaly from
+// the tape: the drift's end follows from them without solving again, and the
+// kicks' positions from the Sun kicks' momenta, so no pair sum and no Kepler
+// iteration is repeated.
+template <int SB, int PL>
 __global__ __launch_bounds__(64) void k_adj_bwd(AdjArgs a) {
-  const Lane<SB> L = lane_of<SB>(a);
-  const int gl = blockIdx.x * 64 + (threadIdx.x & 63);
-  double x, y, z, vx, vy, vz, m;
-  load_state<SB>(a, L, x, y, z, vx, vy, vz, m);  // for the masses
-  const double m0 = L.s < a.nsys ? a.m0[L.s] : 1.0, Gm0 = a.G * m0;
+  const Lane<SB, PL> L = lane_of<SB, PL>(a);
   double lx = 0.0, ly = 0.0, lz = 0.0, lvx = 0.0, lvy = 0.0, lvz = 0.0, lm = 0.0;
   if (L.act) {
     lx = a.gxT[3 * L.row];
@@ -245,12 +301,12 @@ __global__ __launch_bounds__(64) void k_adj_bwd(AdjArgs a) {
     lvy = a.gvT[3 * L.row + 1];
     lvz = a.gvT[3 * L.row + 2];
   }
+  const bool wr = L.act && L.p == 0;
+  const double hm0 = a.h / L.m0, hmm = hm0 * L.m;
   unsigned fl = 0u;
-  const int lane = threadIdx.x & 63;
   for (int c = a.C - 1; c >= 0; --c) {
     const int t0 = c * a.K, t1 = min(a.T, t0 + a.K);
-    x = 1.0e3 + lane;
-    y = z = vx = vy = vz = 0.0;
+    double x = far_x(L), y = 0.0, z = 0.0, vx = 0.0, vy = 0.0, vz = 0.0;
     if (L.act) {
       const double* cp = a.ckpt + (size_t)c * 6 * a.nb;
       x = cp[L.row];
@@ -261,68 +317,70 @@ __global__ __launch_bounds__(64) void k_adj_bwd(AdjArgs a) {
       vz = cp[5 * a.nb + L.row];
     }
     for (int t = t0; t < t1; ++t) {
-      double* tp = a.tape + (size_t)(t - t0) * 6 * a.nlanes;
-      tp[gl] = x;
-      tp[a.nlanes + gl] = y;
-      tp[2 * a.nlanes + gl] = z;
-      tp[3 * a.nlanes + gl] = vx;
-      tp[4 * a.nlanes + gl] = vy;
-      tp[5 * a.nlanes + gl] = vz;
-      free_step<SB>(a, L.act, Gm0, m0, m, x, y, z, vx, vy, vz, fl);
+      double x2[3], v1[3], sK;
+      free_step<SB, PL, false>(a, L, 0.0, x, y, z, vx, vy, vz, x2, v1, sK, fl);
+      if (wr) {
+        double* tp = a.tape + (size_t)(t - t0) * 7 * a.nb + L.row;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          tp[k * a.nb] = x2[k];
+          tp[(3 + k) * a.nb] = v1[k];
+        }
+        tp[6 * a.nb] = sK;
+      }
     }
+    __syncthreads();  // the tape is read by every lane of a body
     for (int t = t1 - 1; t >= t0; --t) {
-      const double* tp = a.tape + (size_t)(t - t0) * 6 * a.nlanes;
-      // recompute the step's intermediate states
-      double px = tp[gl], py = tp[a.nlanes + gl], pz = tp[2 * a.nlanes + gl];
-      double qx = tp[3 * a.nlanes + gl], qy = tp[4 * a.nlanes + gl], qz = tp[5 * a.nlanes + gl];
-      const double xa[3] = {px, py, pz};  // positions of the first kick
-      double ax, ay, az;
-      seg_acc<SB>(a.G, px, py, pz, m, ax, ay, az);
-      qx += a.h * ax;
-      qy += a.h * ay;
-      qz += a.h * az;
-      const double v1[3] = {qx, qy, qz};  // velocities of the first Sun kick
-      double Px = seg_sum<SB>(m * qx), Py = seg_sum<SB>(m * qy), Pz = seg_sum<SB>(m * qz);
-      px += (a.h / m0) * Px;
-      py += (a.h / m0) * Py;
-      pz += (a.h / m0) * Pz;
-      const double x2[3] = {px, py, pz};  // pre-drift state (x2, v1)
-      double sK = 0.0;
-      if (L.act) kepler_drift(Gm0, a.dt, px, py, pz, qx, qy, qz, a.max_iter, &sK);
-      const double v3[3] = {qx, qy, qz};  // velocities of the second Sun kick
-      Px = seg_sum<SB>(m * qx);
-      Py = seg_sum<SB>(m * qy);
-      Pz = seg_sum<SB>(m * qz);
-      px += (a.h / m0) * Px;
-      py += (a.h / m0) * Py;
-      pz += (a.h / m0) * Pz;  // (px, py, pz): positions of the second kick
+      double x2[3] = {far_x(L), 0.0, 0.0}, v1[3] = {0.0, 0.0, 0.0}, sK = 0.0;
+      if (L.act) {
+        const double* tp = a.tape + (size_t)(t - t0) * 7 * a.nb + L.row;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          x2[k] = tp[k * a.nb];
+          v1[k] = tp[(3 + k) * a.nb];
+        }
+        sK = tp[6 * a.nb];
+      }
+      // the drift's end, and the positions of both kicks
+      KeplerAt K{};
+      double v3[3] = {0.0, 0.0, 0.0}, x4[3] = {x2[0], x2[1], x2[2]}, xa[3];
+      if (L.act) {
+        K = kepler_at(L.Gm0, a.dt, x2, v1, sK);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          x4[k] = K.f * x2[k] + K.g * v1[k];
+          v3[k] = K.fd * x2[k] + K.gd * v1[k];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        xa[k] = x2[k] - hm0 * seg_sum<SB, PL>(L.m * v1[k]);
+        x4[k] += hm0 * seg_sum<SB, PL>(L.m * v3[k]);
+      }
       // second kick: x4 -> v5 = v3 + h a(x4)
       double gx = lx, gy = ly, gz = lz;
-      kick_vjp<SB>(a.G, a.h, px, py, pz, m, lvx, lvy, lvz, gx, gy, gz, lm);
+      kick_vjp<SB, PL>(a.G, a.h, L, x4[0], x4[1], x4[2], lvx, lvy, lvz, gx, gy, gz, lm);
       // second Sun kick: x4 = x3 + h P(v3)/m0
-      double S0 = seg_sum<SB>(gx), S1 = seg_sum<SB>(gy), S2 = seg_sum<SB>(gz);
-      double w3x = lvx + a.h * m / m0 * S0, w3y = lvy + a.h * m / m0 * S1,
-             w3z = lvz + a.h * m / m0 * S2;
-      lm += a.h / m0 * (v3[0] * S0 + v3[1] * S1 + v3[2] * S2);
+      double S0 = seg_sum<SB, PL>(gx), S1 = seg_sum<SB, PL>(gy), S2 = seg_sum<SB, PL>(gz);
+      const double lv3[3] = {lvx + hmm * S0, lvy + hmm * S1, lvz + hmm * S2};
+      lm += hm0 * (v3[0] * S0 + v3[1] * S1 + v3[2] * S2);
       // drift
-      double l2[3] = {gx, gy, gz}, lv1[3] = {w3x, w3y, w3z};
+      double l2[3] = {gx, gy, gz}, lv1[3] = {lv3[0], lv3[1], lv3[2]};
       if (L.act) {
-        const double lx3[3] = {gx, gy, gz}, lv3[3] = {w3x, w3y, w3z};
-        const double vpre[3] = {v1[0], v1[1], v1[2]};
-        kepler_vjp(Gm0, a.dt, x2, vpre, sK, lx3, lv3, l2, lv1);
+        const double lx3[3] = {gx, gy, gz};
+        kepler_vjp(L.Gm0, K, x2, v1, sK, lx3, lv3, l2, lv1);
       }
       // first Sun kick: x2 = x + h P(v1)/m0
-      S0 = seg_sum<SB>(l2[0]);
-      S1 = seg_sum<SB>(l2[1]);
-      S2 = seg_sum<SB>(l2[2]);
-      double w1x = lv1[0] + a.h * m / m0 * S0, w1y = lv1[1] + a.h * m / m0 * S1,
-             w1z = lv1[2] + a.h * m / m0 * S2;
-      lm += a.h / m0 * (v1[0] * S0 + v1[1] * S1 + v1[2] * S2);
+      S0 = seg_sum<SB, PL>(l2[0]);
+      S1 = seg_sum<SB, PL>(l2[1]);
+      S2 = seg_sum<SB, PL>(l2[2]);
+      const double w1x = lv1[0] + hmm * S0, w1y = lv1[1] + hmm * S1, w1z = lv1[2] + hmm * S2;
+      lm += hm0 * (v1[0] * S0 + v1[1] * S1 + v1[2] * S2);
       // first kick: v1 = v + h a(x)
       gx = l2[0];
       gy = l2[1];
       gz = l2[2];
-      kick_vjp<SB>(a.G, a.h, xa[0], xa[1], xa[2], m, w1x, w1y, w1z, gx, gy, gz, lm);
+      kick_vjp<SB, PL>(a.G, a.h, L, xa[0], xa[1], xa[2], w1x, w1y, w1z, gx, gy, gz, lm);
       lx = gx;
       ly = gy;
       lz = gz;
@@ -331,8 +389,9 @@ __global__ __launch_bounds__(64) void k_adj_bwd(AdjArgs a) {
       lvz = w1z;
       if (!L.act) lx = ly = lz = lvx = lvy = lvz = lm = 0.0;
     }
+    __syncthreads();  // the next segment writes the tape again
   }
-  if (L.act) {
+  if (wr) {
     a.gx0[3 * L.row] = lx;
     a.gx0[3 * L.row + 1] = ly;
     a.gx0[3 * L.row + 2] = lz;
@@ -342,6 +401,69 @@ __global__ __launch_bounds__(64) void k_adj_bwd(AdjArgs a) {
     a.gm[L.row] = lm;
   }
   if (fl) atomicOr(a.flags, fl);
+}
+
+AdjArgs adj_args(const BatchWs& b, const StepConsts& c, int T, int K, double* ckpt) {
+  AdjArgs a{};
+  a.xm = b.xm;
+  a.vv = b.vv;
+  a.off = b.off;
+  a.m0 = b.m0;
+  a.ckpt = ckpt;
+  a.flags = &b.st->flags;
+  a.nsys = b.nsys;
+  a.T = T;
+  a.K = K;
+  a.C = (T + K - 1) / K;
+  a.nb = b.nb;
+  a.G = c.G;
+  a.dt = c.dt;
+  a.h = c.h;
+  a.n1 = c.n1;
+  a.n2 = c.n2;
+  a.absdt = fabs(c.dt);
+  a.max_iter = c.kepler_max_iter;
+  return a;
+}
+
+// The layout for nsys systems of sb bodies' lanes: the partner lanes that
+// shorten a step's chain, up to the number of waves where their copies' work
+// costs as much.  Systems of 8, 64 steps forward / backward in us, spread
+// against one lane per body (205 / 430 from 1024 to 8192 systems): 1024 systems
+// 121 / 246, 2048 175 / 378, 3072 286 / 562; systems of 16 at 3072: 388 / 815
+// against 406 / 813, of 32: 940 / 2454 against 983 / 2766.
+template <int SB>
+void adj_launch(const AdjArgs& a, bool bwd, hipStream_t s) {
+  constexpr int kSpread = SB <= 8 ? 2048 : 3072;  // waves
+  constexpr int PL = SB < 64 / SB ? SB : 64 / SB;
+  const int per = 64 / (SB * PL);  // systems per wave, spread
+  const int ws = (a.nsys + per - 1) / per;
+  const dim3 blk(64);
+  if (PL > 1 && ws <= kSpread) {
+    if (bwd)
+      hipLaunchKernelGGL((k_adj_bwd<SB, PL>), dim3(ws), blk, 0, s, a);
+    else
+      hipLaunchKernelGGL((k_adj_fwd<SB, PL>), dim3(ws), blk, 0, s, a);
+  } else {
+    const dim3 g((a.nsys + 64 / SB - 1) / (64 / SB));
+    if (bwd)
+      hipLaunchKernelGGL((k_adj_bwd<SB, 1>), g, blk, 0, s, a);
+    else
+      hipLaunchKernelGGL((k_adj_fwd<SB, 1>), g, blk, 0, s, a);
+  }
+}
+
+hipError_t adj_run(const AdjArgs& a, int sb, bool bwd, hipStream_t s) {
+  switch (sb) {
+    case 1: adj_launch<1>(a, bwd, s); break;
+    case 2: adj_launch<2>(a, bwd, s); break;
+    case 4: adj_launch<4>(a, bwd, s); break;
+    case 8: adj_launch<8>(a, bwd, s); break;
+    case 16: adj_launch<16>(a, bwd, s); break;
+    case 32: adj_launch<32>(a, bwd, s); break;
+    default: adj_launch<64>(a, bwd, s); break;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -354,86 +476,22 @@ int adj_segment_lanes(int max_n) {
 
 hipError_t adj_forward(const BatchWs& b, const StepConsts& c, int sb, int T, int K, double* ckpt,
                        hipStream_t s) {
-  AdjArgs a{};
-  a.xm = b.xm;
-  a.vv = b.vv;
-  a.off = b.off;
-  a.m0 = b.m0;
-  a.ckpt = ckpt;
-  a.flags = &b.st->flags;
-  a.nsys = b.nsys;
-  a.T = T;
-  a.K = K;
-  a.C = (T + K - 1) / K;
-  a.nb = b.nb;
-  a.G = c.G;
-  a.dt = c.dt;
-  a.h = c.h;
-  a.n1 = c.n1;
-  a.n2 = c.n2;
-  a.absdt = fabs(c.dt);
-  a.max_iter = c.kepler_max_iter;
-  const int W = 64 / sb;
-  const dim3 g((b.nsys + W - 1) / W), blk(64);
-  switch (sb) {
-    case 1: hipLaunchKernelGGL(k_adj_fwd<1>, g, blk, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_adj_fwd<2>, g, blk, 0, s, a); break;
-    case 4: hipLaunchKernelGGL(k_adj_fwd<4>, g, blk, 0, s, a); break;
-    case 8: hipLaunchKernelGGL(k_adj_fwd<8>, g, blk, 0, s, a); break;
-    case 16: hipLaunchKernelGGL(k_adj_fwd<16>, g, blk, 0, s, a); break;
-    case 32: hipLaunchKernelGGL(k_adj_fwd<32>, g, blk, 0, s, a); break;
-    default: hipLaunchKernelGGL(k_adj_fwd<64>, g, blk, 0, s, a); break;
-  }
-  return hipGetLastError();
+  return adj_run(adj_args(b, c, T, K, ckpt), sb, false, s);
 }
 
-size_t adj_tape_bytes(int nsys, int sb, int K) {
-  const int W = 64 / sb;
-  const size_t nl = (size_t)((nsys + W - 1) / W) * 64;
-  return nl * 6 * (size_t)K * sizeof(double);
-}
+size_t adj_tape_bytes(int64_t nb, int K) { return (size_t)nb * 7 * (size_t)K * sizeof(double); }
 
 hipError_t adj_backward(const BatchWs& b, const StepConsts& c, int sb, int T, int K,
                         double* ckpt, double* tape, const double* gxT, const double* gvT,
                         double* gx0, double* gv0, double* gm, hipStream_t s) {
-  AdjArgs a{};
-  a.xm = b.xm;
-  a.vv = b.vv;
-  a.off = b.off;
-  a.m0 = b.m0;
-  a.ckpt = ckpt;
+  AdjArgs a = adj_args(b, c, T, K, ckpt);
   a.tape = tape;
   a.gxT = gxT;
   a.gvT = gvT;
   a.gx0 = gx0;
   a.gv0 = gv0;
   a.gm = gm;
-  a.flags = &b.st->flags;
-  a.nsys = b.nsys;
-  a.T = T;
-  a.K = K;
-  a.C = (T + K - 1) / K;
-  a.nb = b.nb;
-  a.G = c.G;
-  a.dt = c.dt;
-  a.h = c.h;
-  a.n1 = c.n1;
-  a.n2 = c.n2;
-  a.absdt = fabs(c.dt);
-  a.max_iter = c.kepler_max_iter;
-  const int W = 64 / sb;
-  a.nlanes = ((b.nsys + W - 1) / W) * 64;
-  const dim3 g((b.nsys + W - 1) / W), blk(64);
-  switch (sb) {
-    case 1: hipLaunchKernelGGL(k_adj_bwd<1>, g, blk, 0, s, a); break;
-    case 2: hipLaunchKernelGGL(k_adj_bwd<2>, g, blk, 0, s, a); break;
-    case 4: hipLaunchKernelGGL(k_adj_bwd<4>, g, blk, 0, s, a); break;
-    case 8: hipLaunchKernelGGL(k_adj_bwd<8>, g, blk, 0, s, a); break;
-    case 16: hipLaunchKernelGGL(k_adj_bwd<16>, g, blk, 0, s, a); break;
-    case 32: hipLaunchKernelGGL(k_adj_bwd<32>, g, blk, 0, s, a); break;
-    default: hipLaunchKernelGGL(k_adj_bwd<64>, g, blk, 0, s, a); break;
-  }
-  return hipGetLastError();
+  return adj_run(a, sb, true, s);
 }
 
 }  // namespace genga

@@ -34,28 +34,48 @@ __device__ __forceinline__ void stumpff45(double z, double c2, double c3, double
   }
 }
 
-// Reverse of the Kepler drift: (x0, v0) -> (x1, v1).  In: pre-drift state,
-// the converged s and the output adjoints; out: the input adjoints.
-__device__ __forceinline__ void kepler_vjp(double mu, double dt, const double x0[3],
-                                           const double v0[3], double s, const double lx1[3],
-                                           const double lv1[3], double lx0[3], double lv0[3]) {
-  // 1/r0 and 1/r are formed once and multiplied in
-  const double r0 = sqrt(x0[0] * x0[0] + x0[1] * x0[1] + x0[2] * x0[2]);
-  const double ir0 = 1.0 / r0;
-  const double eta = x0[0] * v0[0] + x0[1] * v0[1] + x0[2] * v0[2];
+// The Kepler drift at its converged universal anomaly s: what the reverse
+// needs of it, formed once (1/r0 and 1/r are multiplied in).
+struct KeplerAt {
+  double ir0, eta, beta, G0, G1, G2, G3, G4, G5, r0, ir, f, g, fd, gd;
+};
+__device__ __forceinline__ KeplerAt kepler_at(double mu, double dt, const double x0[3],
+                                              const double v0[3], double s) {
+  KeplerAt k;
+  k.r0 = sqrt(x0[0] * x0[0] + x0[1] * x0[1] + x0[2] * x0[2]);
+  k.ir0 = 1.0 / k.r0;
+  k.eta = x0[0] * v0[0] + x0[1] * v0[1] + x0[2] * v0[2];
   const double vv = v0[0] * v0[0] + v0[1] * v0[1] + v0[2] * v0[2];
-  const double beta = 2.0 * mu * ir0 - vv;
+  k.beta = 2.0 * mu * k.ir0 - vv;
   double c0, c1, c2, c3, c4, c5;
-  const double zz = beta * s * s;
+  const double zz = k.beta * s * s;
   stumpff(zz, c0, c1, c2, c3);
   stumpff45(zz, c2, c3, c4, c5);
   const double s2 = s * s;
-  const double G0 = c0, G1 = s * c1, G2 = s2 * c2, G3 = s2 * s * c3, G4 = s2 * s2 * c4,
-               G5 = s2 * s2 * s * c5;
-  const double r = r0 * G0 + eta * G1 + mu * G2;
-  const double ir = 1.0 / r;
-  const double f = 1.0 - mu * G2 * ir0, g = dt - mu * G3;
-  const double fd = -mu * G1 * ir * ir0, gd = 1.0 - mu * G2 * ir;
+  k.G0 = c0;
+  k.G1 = s * c1;
+  k.G2 = s2 * c2;
+  k.G3 = s2 * s * c3;
+  k.G4 = s2 * s2 * c4;
+  k.G5 = s2 * s2 * s * c5;
+  const double r = k.r0 * k.G0 + k.eta * k.G1 + mu * k.G2;
+  k.ir = 1.0 / r;
+  k.f = 1.0 - mu * k.G2 * k.ir0;
+  k.g = dt - mu * k.G3;
+  k.fd = -mu * k.G1 * k.ir * k.ir0;
+  k.gd = 1.0 - mu * k.G2 * k.ir;
+  return k;
+}
+
+// Reverse of the Kepler drift (x0, v0) -> (x1, v1).  In: pre-drift state,
+// the drift at its converged s and the output adjoints; out: the input
+// adjoints.
+__device__ __forceinline__ void kepler_vjp(double mu, const KeplerAt& k, const double x0[3],
+                                           const double v0[3], double s, const double lx1[3],
+                                           const double lv1[3], double lx0[3], double lv0[3]) {
+  const double ir0 = k.ir0, eta = k.eta, beta = k.beta, r0 = k.r0, ir = k.ir;
+  const double G0 = k.G0, G1 = k.G1, G2 = k.G2, G3 = k.G3, G4 = k.G4, G5 = k.G5;
+  const double f = k.f, g = k.g, fd = k.fd, gd = k.gd;
   // scalar adjoints of f, g, fdot, gdot
   const double wf = x0[0] * lx1[0] + x0[1] * lx1[1] + x0[2] * lx1[2];
   const double wg = v0[0] * lx1[0] + v0[1] * lx1[1] + v0[2] * lx1[2];
@@ -97,6 +117,12 @@ __device__ __forceinline__ void kepler_vjp(double mu, double dt, const double x0
     lx0[k] = f * lx1[k] + fd * lv1[k] + cx * x0[k] + beta_ * v0[k];
     lv0[k] = g * lx1[k] + gd * lv1[k] + beta_ * x0[k] - 2.0 * bb * v0[k];
   }
+}
+
+__device__ __forceinline__ void kepler_vjp(double mu, double dt, const double x0[3],
+                                           const double v0[3], double s, const double lx1[3],
+                                           const double lv1[3], double lx0[3], double lv0[3]) {
+  kepler_vjp(mu, kepler_at(mu, dt, x0, v0, s), x0, v0, s, lx1, lv1, lx0, lv0);
 }
 
 }  // namespace genga

@@ -61,28 +61,6 @@ __device__ __forceinline__ unsigned long long readlane_u64(unsigned long long v,
   return ((unsigned long long)hi << 32) | lo;
 }
 
-// The halves of a double exchanged between rows 2r and 2r + 1 (W = 16) or
-// between the two halves of the wave (W = 32); returns the lane's value plus
-// its partner's, the pair ordered by row so that both partners hold the same
-// bits.
-template <int W>
-__device__ __forceinline__ double swap_sum(double v) {
-  const int2 p = *reinterpret_cast<int2*>(&v);
-  int2 lo, hi;
-  if (W == 16) {
-    const auto a = __builtin_amdgcn_permlane16_swap(p.x, p.x, false, false);
-    const auto b = __builtin_amdgcn_permlane16_swap(p.y, p.y, false, false);
-    lo = make_int2(a[0], b[0]);
-    hi = make_int2(a[1], b[1]);
-  } else {
-    const auto a = __builtin_amdgcn_permlane32_swap(p.x, p.x, false, false);
-    const auto b = __builtin_amdgcn_permlane32_swap(p.y, p.y, false, false);
-    lo = make_int2(a[0], b[0]);
-    hi = make_int2(a[1], b[1]);
-  }
-  return *reinterpret_cast<double*>(&lo) + *reinterpret_cast<double*>(&hi);
-}
-
 // Sum over the lanes of one system, on every lane: the butterfly over lane
 // distances 1, 2 (DPP quad permutes), 4, 8 (DPP half-row and row mirrors,
 // which pair the same partial sums as lane ^ 4 and lane ^ 8 once those are

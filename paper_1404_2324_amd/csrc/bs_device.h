@@ -281,6 +281,28 @@ constexpr int kDppRowMirror = 0x140;      // lane 15 - i inside each row
 constexpr int kDppRowShr2 = 0x112;      // row_shr:2: lane - 2 inside the row
 constexpr int kDppRowShr1 = 0x111;      // row_shr:1: lane - 1 inside the row
 
+// The halves of a double exchanged between rows 2r and 2r + 1 (W = 16) or
+// between the two halves of the wave (W = 32); returns the lane's value plus
+// its partner's, the pair ordered by row so that both partners hold the same
+// bits.
+template <int W>
+__device__ __forceinline__ double swap_sum(double v) {
+  const int2 p = *reinterpret_cast<int2*>(&v);
+  int2 lo, hi;
+  if (W == 16) {
+    const auto a = __builtin_amdgcn_permlane16_swap(p.x, p.x, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(p.y, p.y, false, false);
+    lo = make_int2(a[0], b[0]);
+    hi = make_int2(a[1], b[1]);
+  } else {
+    const auto a = __builtin_amdgcn_permlane32_swap(p.x, p.x, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(p.y, p.y, false, false);
+    lo = make_int2(a[0], b[0]);
+    hi = make_int2(a[1], b[1]);
+  }
+  return *reinterpret_cast<double*>(&lo) + *reinterpret_cast<double*>(&hi);
+}
+
 // (1-K)-weighted pair factor f of H_A (Eq. 1 gradient, without the partner's
 // mass) times d = x_j - x_b, or 0 where use is false.  Beyond rc_ij
 // (q2 >= near2, a margin far above the rounding of y) the term is exactly 0

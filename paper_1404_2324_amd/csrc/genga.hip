@@ -1008,7 +1008,7 @@ size_t genga_adj_buffer_bytes(genga_ctx* ctx, int64_t nsteps, int ckpt_every) {
   const int K = (int)std::min<int64_t>(ckpt_every, nsteps);
   if (adj_hybrid(ctx))
     return adj_ckpt_bytes(ctx, nsteps, ckpt_every) + hadj_work_bytes(ctx->b.nsys, K);
-  return adj_ckpt_bytes(ctx, nsteps, ckpt_every) + adj_tape_bytes(ctx->b.nsys, ctx->sb, K);
+  return adj_ckpt_bytes(ctx, nsteps, ckpt_every) + adj_tape_bytes(ctx->b.nb, K);
 }
 
 int genga_adj_forward(genga_ctx* ctx, int64_t nsteps, int ckpt_every, void* d_buffer,

@@ -346,7 +346,7 @@ hipError_t hadj_backward(const BatchWs& b, const StepConsts& c, int T, int K, do
                          double* gv0, double* gm, hipStream_t s);
 
 int adj_segment_lanes(int max_n);
-size_t adj_tape_bytes(int nsys, int sb, int K);
+size_t adj_tape_bytes(int64_t nb, int K);
 // T steps of the encounter-free map on the batched state, keeping the state
 // every K steps in ckpt ([ceil(T/K)][6][nb]).
 hipError_t adj_forward(const BatchWs& b, const StepConsts& c, int sb, int T, int K, double* ckpt,

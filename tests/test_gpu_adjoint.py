@@ -188,3 +188,72 @@ def test_encounter_free_map_reuses_its_context():
         ref.close()
     assert seen[0] == seen[1]
     assert gp.encounter_free == 0
+
+
+def _spaced(sizes, seed):
+    """Systems of the given sizes on nearly circular orbits 0.1 apart (farther
+    than the critical radii of Eq. 6, below 0.036 here)."""
+    rng = np.random.default_rng(seed)
+    xs, us, ms = [], [], []
+    for n in sizes:
+        a = 0.5 + 0.1 * np.arange(n) + rng.uniform(0, 0.01, n)
+        m = np.exp(rng.uniform(np.log(1e-7), np.log(1e-6), n))
+        x, u = W.elements_to_cartesian(1.0 + m, a, rng.uniform(0, 0.01, n),
+                                       rng.uniform(0, 0.05, n), *rng.uniform(0, 6.28, (3, n)))
+        v = O.helio_to_dem(O.params(), m, u)
+        xs.append(x)
+        us.append(v)
+        ms.append(m)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    return off, np.ones(len(sizes)), np.concatenate(ms), np.concatenate(xs), np.concatenate(us)
+
+
+def _grad(off, m0s, m, x, v, gx, gv, T, K):
+    sim = G.BatchedSimulation(off, m0s, m, x, v, _gp(), coords="dem")
+    sim.adj_forward(T, K)
+    xT, vT = sim.state("dem")
+    g = sim.adj_backward(gx, gv)
+    sim.check()
+    return [t.cpu().numpy() for t in (xT, vT, *g)]
+
+
+# largest sizes at the edges of every lane layout, each with a smaller system
+# beside it and a number of systems that leaves the last wave partly empty
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 64])
+def test_adjoint_lane_layouts_match_oracle(n):
+    _say("adjoint layout n", n)
+    sizes = [n, max(1, n // 2), n]
+    off, m0s, m, x, v = _spaced(sizes, 40 + n)
+    rng = np.random.default_rng(n)
+    gx, gv = rng.standard_normal((2,) + x.shape)
+    T, K = 20, 8
+    xT, vT, gx0, gv0, gm = _grad(off, m0s, m, x, v, gx, gv, T, K)
+    p = O.params(encounter_free=1)
+    for s in range(len(sizes)):
+        a, b = off[s], off[s + 1]
+        xo, vo = O.free_step(p, m[a:b], x[a:b], v[a:b], T)
+        assert np.abs(xT[a:b] - xo).max() <= 1e-12 * np.abs(xo).max()
+        assert np.abs(vT[a:b] - vo).max() <= 1e-12 * np.abs(vo).max()
+        o = O.free_adjoint(p, m[a:b], x[a:b], v[a:b], T, gx[a:b], gv[a:b])
+        for g, q in zip((gx0[a:b], gv0[a:b], gm[a:b]), o):
+            assert np.abs(g - q).max() <= 1e-9 * np.abs(q).max()
+
+
+# enough systems that the layout with one lane per body runs: its results are
+# those of the same systems alone
+@pytest.mark.parametrize("n,copies", [(2, 49300), (4, 12400), (8, 3100), (16, 3100), (32, 3100)])
+def test_adjoint_dense_layout_equals_spread(n, copies):
+    _say("adjoint dense layout n", n)
+    sizes = [n, n - 1]
+    off, m0s, m, x, v = _spaced(sizes, 60 + n)
+    rng = np.random.default_rng(n)
+    gx, gv = rng.standard_normal((2,) + x.shape)
+    one = _grad(off, m0s, m, x, v, gx, gv, 6, 4)
+    r = copies // 2
+    big = np.concatenate([[0], np.cumsum(sizes * r)]).astype(np.int32)
+    t = [np.tile(q, (r,) + (1,) * (q.ndim - 1)) for q in (m, x, v, gx, gv)]
+    many = _grad(big, np.ones(2 * r), *t, 6, 4)
+    k = int(off[-1])
+    for a, b in zip(one, many):
+        for at in (0, (r // 2) * k, (r - 1) * k):
+            assert np.abs(b[at:at + k] - a).max() <= 1e-12 * np.abs(a).max()
