@@ -86,15 +86,20 @@ __device__ __forceinline__ void block_sum3(double& a, double& b, double& c, doub
 // adds the splits of each body in a fixed order and applies the per-body
 // epilogue.
 // Two shapes (waves per workgroup, splits x padded bodies aimed for), chosen
-// by size (measured): below kPairBigN 16 waves and 16384 (2048 bodies: 8
-// splits, 4096 waves; the launch floor dominates there), from kPairBigN on 8
-// waves and 65536 (16384 bodies: 4 splits, 1024 workgroups of 8 waves,
-// 21.1 against 18.6 TFLOP/s with the small-system shape).
+// by size: up to 2048 padded bodies 16 waves and 16384 (2048 bodies: 8
+// splits, 4096 waves; the launch floor dominates there), beyond 8 waves and up
+// to 16 splits, so that the workgroups are many and small against the 256
+// compute units (5000 bodies: 16 waves and two splits left 96 of them idle).
+// Acceleration call, us, this shape against 16 waves and 16384: 2048 bodies 13.4
+// against 12.5 (kept there), 3000 19.1 against 23.5, 4096 26.7 against 30.0,
+// 5000 34.4 against 59.1, 6144 45.2 against 59.7.  16384 bodies: 217 with 16
+// splits, 218 with 8, 230 with 4; 8 from there on, for the partial sums' size.
 constexpr int kPairW = 16;                     // waves per workgroup, small systems
 constexpr int kPairTarget = 16384;
 constexpr int kPairWBig = 8;                   // waves per workgroup, large systems
-constexpr int kPairTargetBig = 65536;
-constexpr int kPairBigN = 8192;                // padded bodies from which the large shape runs
+constexpr int kPairTargetBig = 131072;
+constexpr int kPairSplitsBig = 16;             // most splits of large systems
+constexpr int kPairBigN = 2048;                // padded bodies beyond which the large shape runs
 constexpr int kPairBlock = 64;                 // i-bodies per workgroup (one per lane)
 constexpr int kPairU = 2;                      // partners per prefetched batch
 constexpr int kFinThreads = 64;                // threads of the finishing kernel
@@ -131,10 +136,11 @@ enum { KICK_CLOSE = 0, KICK_INIT = 1, KICK_ACC = 2 };
 // candidate: its K-weighted term is summed apart ("near") and, outside the
 // accumulation mode, appended to the body's candidate table; every other
 // pair has K = 1 and joins the "far" sum that the next opening kick reuses
-// (KickB).  The common test is one compare against the wave's largest
-// threshold T (over its 64 bodies and its partner range, from the 64-body
-// chunk maxima): below it the term is held out of the far sum by a select,
-// and a wave with any such lane takes the exact test for those lanes.  The
+// (KickB).  The common test is one compare per batch of the batch's least r^2
+// against the wave's largest threshold T (over its 64 bodies and its partner
+// range, from the 64-body chunk maxima); a wave with any lane below it takes
+// the exact test pair by pair.  Bound from 5000 bodies on by FP64 issue (18
+// vector instructions a pair and the reciprocal root's estimate).  The
 // W waves' sums are added in LDS in wave order; the split's sums go to pp.
 template <int MODE, int W>
 __global__ __launch_bounds__(W * 64) void k_pair_part(PairArgs a,
@@ -194,43 +200,45 @@ __global__ __launch_bounds__(W * 64) void k_pair_part(PairArgs a,
 #pragma unroll
       for (int q = 0; q < kPairU; ++q) nxt[q] = xj[k + kPairU + q];
     }
+    // the batch's terms, then one test for all its pairs: with none inside T
+    // (nearly always) they join the far sum as they are; a candidate's term
+    // is taken out of it (set to 0) in the rare branch
+    double dx[kPairU], dy[kPairU], dz[kPairU], r2[kPairU], s[kPairU], rmin = 0.0;
 #pragma unroll
     for (int q = 0; q < kPairU; ++q) {
       const double4 pj = cur[q];
-      const double dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
-      const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-      const double s = m_rinv3(pj.w, r2, c1875, c15);
-      const bool c = r2 < T;
-      const double sf = c ? 0.0 : s;
-      fx = fma(sf, dx, fx);
-      fy = fma(sf, dy, fy);
-      fz = fma(sf, dz, fz);
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(c) != 0ull, 0)) {
+      dx[q] = pj.x - pi.x;
+      dy[q] = pj.y - pi.y;
+      dz[q] = pj.z - pi.z;
+      r2[q] = fma(dx[q], dx[q], fma(dy[q], dy[q], dz[q] * dz[q]));
+      s[q] = m_rinv3(pj.w, r2[q], c1875, c15);
+      rmin = q ? fmin(rmin, r2[q]) : r2[q];
+    }
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(rmin < T) != 0ull, 0)) {
+#pragma unroll
+      for (int q = 0; q < kPairU; ++q) {
         const int j = j0 + k + q;
         const double tj = thr[j];
         // (an empty asm statement keeps the status word's use, and its
         // wait, inside this branch)
         int nlv = nl, stv = stopped;
         asm volatile("" : "+s"(nlv), "+s"(stv));
-        if (c) {
-          if (!(r2 < ti || r2 < tj)) {
-            fx = fma(s, dx, fx);
-            fy = fma(s, dy, fy);
-            fz = fma(s, dz, fz);
-          } else if (i < nlv && j != i && j < nlv) {
-            const double ir = rsqrt_nr(r2);
+        if (r2[q] < ti || r2[q] < tj) {
+          s[q] = 0.0;
+          if (i < nlv && j != i && j < nlv) {
+            const double ir = rsqrt_nr(r2[q]);
             const double ir2 = ir * ir;
             double K = 1.0, dK = 0.0;
-            if (!a.encounter_free) changeover(r2 * ir, fmax(a.rc[i], a.rc[j]), K, dK);
-            const double sn = pj.w * (K * ir2 * ir - dK * ir2);
-            nx += sn * dx;
-            ny += sn * dy;
-            nz += sn * dz;
+            if (!a.encounter_free) changeover(r2[q] * ir, fmax(a.rc[i], a.rc[j]), K, dK);
+            const double sn = cur[q].w * (K * ir2 * ir - dK * ir2);
+            nx += sn * dx[q];
+            ny += sn * dy[q];
+            nz += sn * dz[q];
             if (MODE != KICK_ACC && !a.encounter_free && !stv) {
               const int slot = atomicAdd(&a.ccnt[i], 1);
               if (slot < a.cpb) {
                 a.ctab[(size_t)i * a.cpb + slot] = j;
-                a.cr2[(size_t)i * a.cpb + slot] = r2;
+                a.cr2[(size_t)i * a.cpb + slot] = r2[q];
               } else {
                 atomicOr(&a.st->flags, F_CAND_OVF);
               }
@@ -238,6 +246,12 @@ __global__ __launch_bounds__(W * 64) void k_pair_part(PairArgs a,
           }
         }
       }
+    }
+#pragma unroll
+    for (int q = 0; q < kPairU; ++q) {
+      fx = fma(s[q], dx[q], fx);
+      fy = fma(s[q], dy[q], fy);
+      fz = fma(s[q], dz[q], fz);
     }
     k += kPairU;
   } while (k < L);
@@ -2269,23 +2283,23 @@ size_t massive_ws_bytes(int n, const genga_params& p, bool snap) {
 // Lay the main-mode arrays out in the workspace starting at base (nullptr:
 // only size the layout).  Returns the bytes used.
 // Splits of the partner range per 64-body block of the pair kernel with W
-// waves per workgroup: the largest divisor of np / (W waves x 2 partners)
-// with splits x np at most target, so that small systems still spread over
-// the whole chip (2048 bodies: 8 splits, 4096 waves) and every wave takes
-// whole batches.
-int pair_splits(int np, int W, int target) {
+// waves per workgroup: the largest divisor of np / (W waves x 2 partners), at
+// most `most`, with splits x np at most target, so that small systems still
+// spread over the whole chip (2048 bodies: 8 splits, 4096 waves) and every wave
+// takes whole batches.
+int pair_splits(int np, int W, int target, int most) {
   const int q = np / (W * kPairU);
   int best = 1;
-  for (int d = 1; d <= q; ++d)
+  for (int d = 1; d <= q && d <= most; ++d)
     if (q % d == 0 && (size_t)d * np <= (size_t)target) best = d;
   return best;
 }
 
 // The pair kernel's shape for np padded bodies: waves per workgroup, splits.
 void pair_shape(int np, int* pw, int* njs) {
-  const bool big = np >= kPairBigN;
+  const bool big = np > kPairBigN;
   *pw = big ? kPairWBig : kPairW;
-  *njs = pair_splits(np, *pw, big ? kPairTargetBig : kPairTarget);
+  *njs = pair_splits(np, *pw, big ? kPairTargetBig : kPairTarget, big ? kPairSplitsBig : np);
 }
 
 size_t massive_carve(MassiveWs& w, int n, const genga_params& p, void* base, bool snap) {
@@ -2575,7 +2589,7 @@ hipError_t accel_run(const MassiveWs& w, const StepConsts& c, const double* m, c
 // and candidate counts of up to kNoAllocBodies bodies (116 bytes per padded
 // body), the 64-body chunks' largest thresholds and the pair kernel's partial sums
 // (6 doubles x splits x padded bodies, splits x padded bodies <=
-// kPairTargetBig, the pair kernel's shape being the workspace path's): 5.0 MB.  Each GPU holds its own copy until the process ends;
+// kPairTargetBig, the pair kernel's shape being the workspace path's): 8.2 MB.  Each GPU holds its own copy until the process ends;
 // every call on a GPU uses that GPU's copy, so calls that overlap on one GPU
 // race.  Every byte a call reads is written earlier in the same call.
 constexpr int kNoAllocBodies = kAccelNoAllocMax;
