@@ -9,6 +9,15 @@
 
 namespace genga {
 
+// Orders the LDS and global accesses of one wave's lanes where other waves of
+// the workgroup do not take part: the release and acquire fences of a
+// workgroup barrier around a wave barrier, without its s_barrier.
+__device__ __forceinline__ void wsync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 constexpr int kBsCols = 8;
 constexpr int kBsMaxAttempts = 1 << 16;  // substep attempts per group and step
 

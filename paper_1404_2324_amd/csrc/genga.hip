@@ -105,6 +105,7 @@ struct genga_ctx {
   std::vector<StepConsts> sub;           // main mode: the constants of each sub-step
   hipStream_t stream = nullptr;
   hipStream_t cap = nullptr;
+  hipStream_t side = nullptr;            // test particles: a graph's refinement branch
   hipGraphExec_t g_many = nullptr;
   hipGraphExec_t g_rem[16] = {};  // r steps in one graph, r = 1 .. 15
   int64_t steps = 0;
@@ -126,16 +127,58 @@ static void drop_graphs(genga_ctx* ctx) {
   }
 }
 
+// nsteps steps of test-particle mode on the capture stream, each step's
+// refinement beside the next step on a second branch (tp.hip), which the
+// stream joins before its end.  With few particles the refinement is short and
+// the two passes over the queue and the branch cost more than it: one branch.
+// us a step in graphs of 16, two branches against one: 10^6 particles and 8
+// planets 215 against 289 (310 before, with a one-workgroup scan of the lists),
+// 10^5 152 / 168, 10^4 98 / 114 and 93 / 104 (two draws), 3001 particles and 3
+// planets 84 / 94 and 69 / 49, 1000 particles 85 / 79.
+constexpr int64_t kTpOverlap = 8192;
+static hipError_t record_tp_steps(genga_ctx* ctx, int nsteps, std::vector<hipEvent_t>& ev) {
+  static_assert(kGraphSteps <= kTpSlots, "one planet slot per step of a graph");
+  hipStream_t s = ctx->cap, sr = ctx->side;
+  hipError_t e = hipSuccess;
+  auto ok = [&](hipError_t r) { return (e = r) == hipSuccess; };
+  // work on `to` from here on follows the work so far on `from`
+  auto after = [&](hipStream_t from, hipStream_t to) {
+    hipEvent_t q = nullptr;
+    if (!ok(hipEventCreateWithFlags(&q, hipEventDisableTiming))) return false;
+    ev.push_back(q);
+    return ok(hipEventRecord(q, from)) && ok(hipStreamWaitEvent(to, q, 0));
+  };
+  const bool side = nsteps > 1 && !ctx->c.encounter_free && ctx->t.ntp >= kTpOverlap;
+  for (int k = 0; k < nsteps; ++k) {
+    const bool defer = side && k + 1 < nsteps;
+    if (!ok(massive_step(ctx->w, ctx->sub[0], s, nullptr, ctx->t.slot[k].cnt)) ||
+        !ok(tp_main(ctx->w, ctx->t, ctx->c, k, defer, s)))
+      return e;
+    if (side && k > 0 &&
+        (!after(sr, s) || !ok(tp_late(ctx->w, ctx->t, ctx->c, k, defer, s))))
+      return e;
+    if (defer && !after(s, sr)) return e;
+    if (!ok(tp_refine(ctx->w, ctx->t, ctx->c, k, defer ? sr : s))) return e;
+  }
+  return e;
+}
+
 static int capture(genga_ctx* ctx, int nsteps, hipGraphExec_t* out) {
   hipGraph_t g = nullptr;
+  std::vector<hipEvent_t> ev;
+  if (ctx->mode == GENGA_TEST && !ctx->side)
+    HIPCHK(hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
   HIPCHK(hipStreamBeginCapture(ctx->cap, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
-  for (int k = 0; k < nsteps && e == hipSuccess; ++k) {
-    for (size_t q = 0; q < ctx->sub.size() && e == hipSuccess; ++q)
-      e = massive_step(ctx->w, ctx->sub[q], ctx->cap);
-    if (e == hipSuccess && ctx->mode == GENGA_TEST) e = tp_step(ctx->w, ctx->t, ctx->c, ctx->cap);
+  if (ctx->mode == GENGA_TEST) {
+    e = record_tp_steps(ctx, nsteps, ev);
+  } else {
+    for (int k = 0; k < nsteps && e == hipSuccess; ++k)
+      for (size_t q = 0; q < ctx->sub.size() && e == hipSuccess; ++q)
+        e = massive_step(ctx->w, ctx->sub[q], ctx->cap);
   }
   hipError_t e2 = hipStreamEndCapture(ctx->cap, &g);
+  for (hipEvent_t q : ev) (void)hipEventDestroy(q);
   if (e != hipSuccess || e2 != hipSuccess) {
     if (g) (void)hipGraphDestroy(g);
     return GENGA_EHIP;
@@ -451,6 +494,7 @@ int genga_step(genga_ctx* ctx, int64_t nsteps) {
   }
   for (int64_t k = 0; k < nsteps / kGraphSteps; ++k) HIPCHK(hipGraphLaunch(ctx->g_many, ctx->stream));
   if (rem) HIPCHK(hipGraphLaunch(ctx->g_rem[rem], ctx->stream));
+  ctx->t.last = ((rem ? rem : kGraphSteps) - 1) & 1;  // the last graph's last step
   ctx->steps += nsteps;
   return GENGA_OK;
 }
@@ -478,8 +522,11 @@ static int step_timed(genga_ctx* ctx, int64_t nsteps, bool all, double* us) {
   hipEvent_t last = nullptr;
   for (int64_t t = 0; t < nsteps && rc == GENGA_OK; ++t) {
     const hipEvent_t* kev = &ev[(size_t)(2 * K * t)];
-    if (massive_step(ctx->w, ctx->sub[0], ctx->stream, kev) != hipSuccess ||
-        (ctx->mode == GENGA_TEST && tp_step(ctx->w, ctx->t, ctx->c, ctx->stream) != hipSuccess))
+    int* tpcnt = ctx->mode == GENGA_TEST ? ctx->t.slot[0].cnt : nullptr;
+    if (massive_step(ctx->w, ctx->sub[0], ctx->stream, kev, tpcnt) != hipSuccess ||
+        (ctx->mode == GENGA_TEST &&
+         (tp_main(ctx->w, ctx->t, ctx->c, 0, false, ctx->stream) != hipSuccess ||
+          tp_refine(ctx->w, ctx->t, ctx->c, 0, ctx->stream) != hipSuccess)))
       rc = GENGA_EHIP;
     last = kev[2 * klast + 1];
   }
@@ -496,6 +543,7 @@ static int step_timed(genga_ctx* ctx, int64_t nsteps, bool all, double* us) {
   for (auto& e : ev)
     if (e) (void)hipEventDestroy(e);
   if (rc != GENGA_OK) return rc;
+  ctx->t.last = 0;
   ctx->steps += nsteps;
   return genga_sync(ctx);
 }
@@ -1069,6 +1117,7 @@ int genga_destroy(genga_ctx* ctx) {
   for (hipGraphExec_t g : ctx->g_rem)
     if (g) (void)hipGraphExecDestroy(g);
   if (ctx->cap) (void)hipStreamDestroy(ctx->cap);
+  if (ctx->side) (void)hipStreamDestroy(ctx->side);
   delete ctx;
   return GENGA_OK;
 }

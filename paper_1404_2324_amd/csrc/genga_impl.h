@@ -113,40 +113,60 @@ struct MassiveWs {
   DevStat* st;
 };
 
-// Test-particle state and the per-step list of particles needing BS.
+constexpr int kTpMaxPlanets = 32;
+constexpr int kTpSlots = 16;       // steps of one captured graph, at most
+
+// The particles of a step that need BS, at the positions of their blocks'
+// regions (256 entries per block of 256 particles).
+struct TpLists {
+  int* idx;             // the particle
+  unsigned* mask;       // its encounter planets (cleared as it finishes)
+  unsigned* emask;      // the same, kept for the encounter report
+  double* rct;          // its critical radius
+  double* y;            // its pre-drift state [6][cap]
+  int *list, *lq, *rq;  // positions: listed by the main pass, by the late pass, left to the wave path
+};
+
+// The planets of one step of a graph, kept for its refinement while their next
+// step runs, and the step's list counts.
+struct TpSlot {
+  double4 *px0, *ppre, *vpre, *pfin;
+  double *rc, *P2;
+  unsigned long long* nstep;
+  int* cnt;             // entries of list, lq, rq
+  double* pl;           // the planets' whole-step BS table
+};
+
+// Test-particle state and the lists of particles needing BS.
 struct TpWs {
   int64_t ntp;
   double* x;            // [3][ntp]
   double* v;            // [3][ntp]
   unsigned* mask;       // candidate planets per particle
-  int* bs_idx;          // listed particles
-  unsigned* bs_mask;    // their encounter planets (cleared as they finish)
-  unsigned* bs_emask;   // the same, kept for the encounter report
+  TpLists lists[2];     // used in turn by the steps of a graph
+  TpSlot slot[kTpSlots];
+  int last;             // the lists of the last step taken
+  unsigned char* busy;  // particles in refinement, left out by the next main pass
   double* enc_d2;       // Hermite minimum of each encounter [nm][ntp]
   double* enc_rc2;      // its threshold r_crit,ij^2 [nm][ntp]
   int nm;               // massive bodies (stride of enc_d2, enc_rc2)
-  double* bs_rct;       // their critical radii
-  double* bs_y;         // their pre-drift state [6][ntp]
   double* rad;          // physical radii: planets [32], then particles [ntp]
   CollRec* coll;        // collision reports, one slot per particle
   int64_t nb, cap;      // 256-particle blocks; list capacity nb * 256
   int* blk_cnt;         // listed particles per block (this step)
-  int* blk_off;         // their prefix sum [nb + 1]
   int* blk_enc;         // encounters per block (this step)
   unsigned long long* blk_enc_tot;  // encounters per block since init
   int* blk_kit;         // largest Kepler iteration count per block
   unsigned long long* khist;  // Kepler iterations per block, cumulative [nb][kKepBins]
   unsigned long long* sub;          // accepted BS substeps per workgroup / wave
-  double* pl;           // planets' whole-step BS table
-  int64_t* rq;          // listed entries left to the wave path (this step)
-  int* rq_cnt;          // their count
-  void* cum;            // the cumulative counters above, cleared at init
+  void* cum;            // the cumulative counters above and busy, cleared at init
   size_t cum_bytes;
 };
 
-constexpr int kTpMaxPlanets = 32;
+constexpr int kTpLateGrid = 256;   // workgroups of the late pass
 constexpr int kTpBs1Grid = 1024;   // workgroups of the whole-step BS attempt
 constexpr int kTpBsGrid = 2048;    // waves of the refinement path
+constexpr int kTpBsWaves = 4;      // waves per workgroup there
 constexpr int kTpSubSlots = kTpBs1Grid + kTpBsGrid;
 
 struct TpCounters {
@@ -203,8 +223,9 @@ hipError_t massive_reset_bodies(const MassiveWs& w, bool clear_radii, hipStream_
 // timestamps of kernel k's dispatch.
 constexpr int kStepKernels = 5;
 constexpr int kSlotPairs = 3;  // the pair kernel's slot
+// tpcnt: test-particle list counts (three) that the step's first kernel clears.
 hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
-                        const hipEvent_t* kev = nullptr);
+                        const hipEvent_t* kev = nullptr, int* tpcnt = nullptr);
 hipError_t massive_energy(const MassiveWs& w, const StepConsts& c, double* dE,
                           double* dL, hipStream_t s);
 // H_B acceleration of positions x (w = mass; x = xs for a context's state).
@@ -243,8 +264,16 @@ hipError_t tp_unpack(const MassiveWs& w, const TpWs& t, const StepConsts& c,
                      double* x, double* v, int coords_out, hipStream_t s);
 hipError_t tp_prime(const MassiveWs& w, const TpWs& t, const StepConsts& c,
                     hipStream_t s);
-hipError_t tp_step(const MassiveWs& w, const TpWs& t, const StepConsts& c,
+// Step k (0 .. kTpSlots - 1) of a graph, after the planets' step (which clears
+// the list counts of slot k): the particles outside the last step's refinement
+// (defer: those that this step leaves to refinement stay out of step k + 1's
+// main pass); those the refinement of step k - 1 held; refinement.
+hipError_t tp_main(const MassiveWs& w, const TpWs& t, const StepConsts& c, int k, bool defer,
                    hipStream_t s);
+hipError_t tp_late(const MassiveWs& w, const TpWs& t, const StepConsts& c, int k, bool defer,
+                   hipStream_t s);
+hipError_t tp_refine(const MassiveWs& w, const TpWs& t, const StepConsts& c, int k,
+                     hipStream_t s);
 // Sums the per-block counters (synchronising).
 hipError_t tp_read_counters(const TpWs& t, TpCounters* h, hipStream_t s);
 // Test-particle rows [nm, nm + ntp) of x and v: finite, or all NaN (removed);

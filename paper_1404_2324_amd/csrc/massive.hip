@@ -419,6 +419,7 @@ struct OpenArgs {
   double* __restrict__ partP2;
   unsigned long long* __restrict__ khist;
   DevStat* __restrict__ st;
+  int* __restrict__ tpcnt;         // test-particle list counts to clear (or null)
   int n, cpb, encounter_free, max_iter;
   double G, h, pf2, m0, mu, dt;
 };
@@ -516,6 +517,7 @@ __global__ __launch_bounds__(kOpenBlock) void k_open_drift(OpenArgs a) {
       threadIdx.x < kKepBins ? a.khist[(size_t)blockIdx.x * kKepBins + threadIdx.x] : 0ull;
   const int itmax0 = a.st->kep_itmax;
   if (threadIdx.x < kKepBins) kh[threadIdx.x] = 0u;
+  if (a.tpcnt && blockIdx.x == 0 && threadIdx.x < 3) a.tpcnt[threadIdx.x] = 0;
   __syncthreads();
   if (a.st->flags & F_NMIN) {
     // fewer than nmin bodies left after the last step: the run has stopped
@@ -822,15 +824,17 @@ __global__ __launch_bounds__(256) void k_encounter_all(EncArgs a) {
 // The first kEncLds pairs are held in LDS; pairs beyond (many-pair regimes,
 // up to the list capacity) are read from the encounter list in place, so
 // the workgroup's LINK array, not the pair count, bounds the grouping.
-template <int NT>
+// N: most bodies; NP: pairs held in LDS.
+template <int NT, int N, int NP>
 struct GroupLds {
-  int link[kGroupMaxN];
-  int first[kGroupMaxN];  // the first end (2 e or 2 e + 1) naming each body
-  int gid[kGroupMaxN];    // group of each root
-  int2 pr[kEncLds];
-  int gsz[kGroupMaxN / 2 + 1];
-  int gof[kGroupMaxN / 2 + 1];  // group offsets, gof[ng] = the member count
-  int roots[kGroupMaxN / 2];
+  static constexpr int kN = N, kPairs = NP;
+  int link[N];
+  int first[N];  // the first end (2 e or 2 e + 1) naming each body
+  int gid[N];    // group of each root
+  int2 pr[NP];
+  int gsz[N / 2 + 1];
+  int gof[N / 2 + 1];  // group offsets, gof[ng] = the member count
+  int roots[N / 2];
   int nroot;
   int shw[NT / 64];
   int chg[2];
@@ -840,8 +844,8 @@ struct GroupLds {
 // returns the number of groups.  gm (LDS, or null): the members by group at
 // the offsets gof.  writer: this workgroup writes the global results.  pf
 // (or null): the list's entry tid, already loaded by the caller.
-template <int NT>
-__device__ __forceinline__ int group_phase(const EncArgs& a, int ne_all, GroupLds<NT>& L,
+template <int NT, class GL>
+__device__ __forceinline__ int group_phase(const EncArgs& a, int ne_all, GL& L,
                                            int* gm, bool writer,
                                            const int2* pf = nullptr) {
   int* link = L.link;
@@ -855,7 +859,7 @@ __device__ __forceinline__ int group_phase(const EncArgs& a, int ne_all, GroupLd
   const int tid = threadIdx.x, lane = tid & 63;
   const int n = a.n;
   const int ne = min(ne_all, a.enc_cap);
-  const int nl = min(ne, kEncLds);  // pairs held in LDS
+  const int nl = min(ne, GL::kPairs);  // pairs held in LDS
   auto pair_at = [&](int e) { return e < nl ? pr[e] : a.encij[e]; };
   auto end_at = [&](int t) {  // end t of the pairs: pair t / 2, first or second body
     const int2 q = pair_at(t >> 1);
@@ -939,7 +943,7 @@ __device__ __forceinline__ int group_phase(const EncArgs& a, int ne_all, GroupLd
   }
   __syncthreads();
   // offsets: exclusive scan of the sizes
-  constexpr int GPER = (kGroupMaxN / 2 + NT - 1) / NT;
+  constexpr int GPER = (GL::kN / 2 + NT - 1) / NT;
   int loc = 0, mx = 0;
   for (int k = 0; k < GPER; ++k) {
     const int g = tid * GPER + k;
@@ -992,7 +996,7 @@ __device__ __forceinline__ int group_phase(const EncArgs& a, int ne_all, GroupLd
 }
 
 __global__ __launch_bounds__(kEncThreads) void k_group(EncArgs a) {
-  __shared__ GroupLds<kEncThreads> L;
+  __shared__ GroupLds<kEncThreads, kGroupMaxN, kEncLds> L;
   if (a.st->flags & F_NMIN) return;  // the run stopped below nmin bodies
   (void)group_phase<kEncThreads>(a, a.st->nenc, L, nullptr, true);
 }
@@ -1027,15 +1031,8 @@ struct BsArgs {
 // without collisions take all of them (speculative depths spread over the
 // waves); every other group is integrated by wave 0 alone while the others
 // wait at the group's closing barrier.  The lanes of that one wave order
-// their LDS and global accesses with wsync: the release and acquire fences
-// of a workgroup barrier around a wave barrier, without the workgroup-wide
-// s_barrier the waiting waves would have to join.
+// their LDS and global accesses with wsync.
 constexpr int kBsWaves = 4;
-__device__ __forceinline__ void wsync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
 
 // ---- groups of more than 64 members ------------------------------------------
 // One wave integrates the group with the BS scheme of the smaller paths (the
@@ -1703,14 +1700,21 @@ __global__ __launch_bounds__(64 * kBsWaves) void k_bs(BsArgs a) {
 // the pairs alone), so no workgroup waits for another before its BS; one
 // also writes the groups, the counts and the cleared candidate table to
 // global memory.
+// LB: waves per SIMD to leave room for; N, NP: most bodies, pairs in LDS.
+// Test-particle mode (up to 32 planets) runs it beside the particles'
+// refinement, whose waves hold half the registers of the SIMDs they are on:
+// LB = 2 and the small tables let it start at once, where the 2048-body form
+// (356 registers, 90 KB of LDS) waited for four free SIMDs on one compute unit.
+template <int N, int NP>
 struct GroupBsLds {
-  GroupLds<64 * kBsWaves> g;
-  int gm[kGroupMaxN];
+  GroupLds<64 * kBsWaves, N, NP> g;
+  int gm[N];
   BsLds b;
 };
-__global__ __launch_bounds__(64 * kBsWaves) void k_group_bs(EncArgs e, BsArgs a) {
+template <int LB, int N, int NP>
+__global__ __launch_bounds__(64 * kBsWaves, LB) void k_group_bs(EncArgs e, BsArgs a) {
   constexpr int NT = 64 * kBsWaves;
-  __shared__ GroupBsLds L;
+  __shared__ GroupBsLds<N, NP> L;
   // the status word, the pair count and the list's first NT entries (a
   // step's pairs are fewer, as a rule) are loaded together; entries past the
   // count are dropped, and any beyond NT are read once the count is known
@@ -2421,7 +2425,7 @@ hipError_t massive_accel(const MassiveWs& w, const StepConsts& c, const double4*
   } while (0)
 
 hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
-                        const hipEvent_t* kev) {
+                        const hipEvent_t* kev, int* tpcnt) {
   OpenArgs o;
   o.xs = w.xs;
   o.xm = w.xm;
@@ -2442,6 +2446,7 @@ hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
   o.partP2 = w.partP2;
   o.khist = w.khist;
   o.st = w.st;
+  o.tpcnt = tpcnt;
   o.n = w.n;
   o.cpb = w.cpb;
   o.encounter_free = c.encounter_free;
@@ -2509,7 +2514,8 @@ hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
       hipLaunchKernelGGL(k_bs, bs_grid, dim3(64 * kBsWaves), 0, s, b);
     } else {
       STEP_LAUNCH(1, k_encounter, dim3(ceil_div(w.n * w.cpb, kVecBlock)), dim3(kVecBlock), e);
-      STEP_LAUNCH(2, k_group_bs, bs_grid, dim3(64 * kBsWaves), e, b);
+      const auto kgb = tpcnt ? k_group_bs<2, kTpMaxPlanets, 512> : k_group_bs<1, kGroupMaxN, kEncLds>;
+      STEP_LAUNCH(2, kgb, bs_grid, dim3(64 * kBsWaves), e, b);
     }
     if (c.phys) {
       // bodies that merged or crossed rcut / rcut_sun leave (not timed per

@@ -5,18 +5,23 @@
 //              the planets' momentum, Kepler drift, Hermite test against the
 //              particle's candidate planets; particles without an encounter
 //              finish the step here (second Sun kick, closing kick, new
-//              candidate mask); the others are compacted into a list.  One
-//              more block, beside the particles' blocks: each planet's
-//              Gragg sequences and extrapolation over the whole step (it
-//              feels only the star inside a particle's group), the same for
-//              every particle that meets it
-//   k_tp_scan  offsets of each block's listed particles (one workgroup)
+//              candidate mask); the others are appended to a list.  One more
+//              block, beside the particles': the planets of the step into its
+//              slot, and each planet's Gragg sequences and extrapolation over
+//              the whole step (it feels only the star inside a particle's
+//              group), the same for every particle that meets it
 //   k_tp_bs1   eight lanes (one per extrapolation column) per particle
 //              meeting one planet: the BS attempt over the whole step with
 //              the planet taken from that table; most passages end here
 //   k_tp_bs    one wave per remaining particle: BS of the particle with the
 //              planets it encounters (planets feel only the star there) with
 //              binary refinement, then the rest of its step
+// A particle feels no other one, so the refinement, which lasts as long as its
+// slowest passage, runs beside the next step's planets and main pass (on a
+// second branch of the graph; it reads the planets of its step from the slot).
+// That step skips the particles still in refinement (busy) and takes them right
+// after it, with the same step code over the queue (k_tp_late, k_tp_bs1 again).
+// The lists are kept twice, used in turn.
 // A particle that comes closer to a planet than the sum of their physical
 // radii during a BS substep is removed there and reported (Sec. 3.3).
 // Counters are kept per block or wave (no same-address atomics on the step
@@ -56,6 +61,8 @@ struct TpArgs {
   const double4* __restrict__ pfin;   // planets at the end of the step
   const double* __restrict__ rc;      // planets' radii of the step
   const double* __restrict__ partP;   // planets' momentum partials (opening kick)
+  const double* __restrict__ P2;      // planets' momentum of the second Sun kick
+  const unsigned long long* __restrict__ nstep;  // steps begun, this one included
   DevStat* __restrict__ st;
   int* __restrict__ bs_idx;           // listed particles
   unsigned* __restrict__ bs_mask;     // their encounter planets
@@ -67,16 +74,22 @@ struct TpArgs {
   const double* __restrict__ rad;     // radii: planets [32], particles [ntp]
   CollRec* __restrict__ coll;         // removal reports
   int* __restrict__ blk_cnt;          // listed particles of each 256-particle block
-  int* __restrict__ blk_off;          // their exclusive prefix sum [nb + 1]
   int* __restrict__ blk_enc;          // encounters of each block, last step
   unsigned long long* __restrict__ blk_enc_tot;
   int* __restrict__ blk_kit;          // largest Kepler iteration count per block
   unsigned long long* __restrict__ khist;  // Kepler iterations per block [nb][bins]
   unsigned long long* __restrict__ sub;  // accepted BS substeps per block / wave
   double* __restrict__ pl;            // planets' full-step BS table
-  int64_t* __restrict__ rq;           // entries left to the wave path
-  int* __restrict__ rq_cnt;           // their count
+  int* __restrict__ list;             // listed entries of the step, in any order
+  int* __restrict__ lq;               // those listed by its late pass
+  int* __restrict__ rq;               // entries left to the wave path
+  int* __restrict__ cnt;              // their counts: list, lq, rq
+  const int* __restrict__ prq;        // the step before: its queue, count and particles
+  const int* __restrict__ prq_cnt;
+  const int* __restrict__ pidx;
+  unsigned char* __restrict__ busy;   // particles the next step's main pass leaves out
   int64_t ntp, cap, nb;
+  int defer;                          // queued particles are refined beside the next step
   int nm, nblk, enc_free, max_iter;
   double G, h, m0, mu, dt, absdt, n2, pf2, tol;
   int max_depth;
@@ -142,13 +155,94 @@ __device__ __forceinline__ void tp_finish(const TpArgs& a, const double4* __rest
   a.mask[k] = msk;
 }
 
+// The planets' states of the step, as kernel arguments of their own: noalias
+// parameters' wave-uniform loads become scalar loads.
+struct TpPlanets {
+  const double4 *px0, *pfin, *ppre, *vpre, *ppost, *vpost;
+  const double* rc;
+};
+
+// What a particle with an encounter leaves for its BS.
+struct TpListed {
+  unsigned emask = 0u;  // the planets it meets; 0: the particle's step is done
+  double x = 0, y = 0, z = 0, vx = 0, vy = 0, vz = 0, rct = 0;
+  int it = 0;  // Kepler iterations, 0 for a particle that took no step
+};
+
+// One particle's step up to its BS.
+__device__ __forceinline__ TpListed tp_particle(const TpArgs& a, const TpPlanets& pl, int64_t k,
+                                                double P1x, double P1y, double P1z, double P2x,
+                                                double P2y, double P2z, unsigned* kh) {
+  TpListed L;
+  double x = a.x[k];
+  if (isnan(x)) return L;
+  double y = a.x[a.ntp + k], z = a.x[2 * a.ntp + k];
+  double vx = a.v[k], vy = a.v[a.ntp + k], vz = a.v[2 * a.ntp + k];
+  const unsigned cmask = a.mask[k];
+  const double rct = a.n2 * a.absdt * sqrt(vx * vx + vy * vy + vz * vz);
+  double ax, ay, az;
+  tp_kick_acc(a, pl.px0, pl.rc, x, y, z, rct, ax, ay, az);
+  vx += a.h * ax;
+  vy += a.h * ay;
+  vz += a.h * az;
+  x += a.h * P1x / a.m0;
+  y += a.h * P1y / a.m0;
+  z += a.h * P1z / a.m0;
+  L.x = x;
+  L.y = y;
+  L.z = z;
+  L.vx = vx;
+  L.vy = vy;
+  L.vz = vz;
+  L.rct = rct;
+  L.it = kepler_drift(a.mu, a.dt, x, y, z, vx, vy, vz, a.max_iter);
+  if (L.it < 0) atomicOr(&a.st->flags, F_KEPLER);
+  atomicAdd(&kh[min(abs(L.it), kKepBins - 1)], 1u);
+  if (!a.enc_free && cmask) {
+    for (int j = 0; j < a.nm; ++j) {
+      if (!(cmask & (1u << j))) continue;
+      const double4 p0 = pl.ppre[j], q0 = pl.vpre[j], p1 = pl.ppost[j], q1 = pl.vpost[j];
+      const double d2 = hermite_dmin2(a.dt, p0.x - L.x, p0.y - L.y, p0.z - L.z,
+                                      q0.x - L.vx, q0.y - L.vy, q0.z - L.vz,
+                                      p1.x - x, p1.y - y, p1.z - z,
+                                      q1.x - vx, q1.y - vy, q1.z - vz);
+      const double rcij = fmax(rct, pl.rc[j]);
+      if (d2 < rcij * rcij) {
+        L.emask |= 1u << j;
+        a.enc_d2[(size_t)j * a.ntp + k] = d2;
+        a.enc_rc2[(size_t)j * a.ntp + k] = rcij * rcij;
+      }
+    }
+  }
+  if (!L.emask) tp_finish(a, pl.pfin, pl.rc, k, x, y, z, vx, vy, vz, rct, P2x, P2y, P2z);
+  return L;
+}
+
+__device__ __forceinline__ void tp_list(const TpArgs& a, int64_t pos, int64_t k,
+                                        const TpListed& L) {
+  a.bs_idx[pos] = (int)k;
+  a.bs_mask[pos] = L.emask;
+  a.bs_emask[pos] = L.emask;
+  a.bs_rct[pos] = L.rct;
+  a.bs_y[pos] = L.x;
+  a.bs_y[a.cap + pos] = L.y;
+  a.bs_y[2 * a.cap + pos] = L.z;
+  a.bs_y[3 * a.cap + pos] = L.vx;
+  a.bs_y[4 * a.cap + pos] = L.vy;
+  a.bs_y[5 * a.cap + pos] = L.vz;
+}
+
+// One lane per particle.  Bound by FP64 issue (1600 vector instructions a
+// particle; 10^6 particles and 8 planets 65 us, where their 104 MB would take 13
+// us).  A block's listed particles go to its own region of the list (which
+// the encounter report reads) and their positions, by one atomic per block, to
+// the step's list: that order does not matter, and it replaced a one-workgroup
+// scan of the blocks' counts (5.5 us) and a search of them per passage.
+__device__ void tp_snap(const TpArgs& a, const TpSlot& q);
 __device__ void tp_plan(const TpArgs& a);
 
-// The planets' arrays come as kernel arguments of their own: as noalias
-// parameters their wave-uniform loads become scalar loads.  A block past
-// the particles' nb blocks (launched with encounters) builds the planets'
-// whole-step table instead, beside the particles' work.
-__global__ __launch_bounds__(256) void k_tp_main(TpArgs a, const double4* __restrict__ px0,
+__global__ __launch_bounds__(256) void k_tp_main(TpArgs a, TpSlot sl,
+                                                 const double4* __restrict__ px0,
                                                  const double4* __restrict__ pfin,
                                                  const double4* __restrict__ ppre,
                                                  const double4* __restrict__ vpre,
@@ -156,6 +250,7 @@ __global__ __launch_bounds__(256) void k_tp_main(TpArgs a, const double4* __rest
                                                  const double4* __restrict__ vpost,
                                                  const double* __restrict__ prc) {
   if ((int64_t)blockIdx.x >= a.nb) {  // the extra block (uniform over the workgroup)
+    tp_snap(a, sl);
     tp_plan(a);
     return;
   }
@@ -170,65 +265,23 @@ __global__ __launch_bounds__(256) void k_tp_main(TpArgs a, const double4* __rest
     P1y += a.partP[4 * b + 1];
     P1z += a.partP[4 * b + 2];
   }
-  const double P2x = a.st->P2[0], P2y = a.st->P2[1], P2z = a.st->P2[2];
-  bool listed = false;
-  unsigned emask = 0u;
-  double xm0 = 0, ym0 = 0, zm0 = 0, vxm = 0, vym = 0, vzm = 0, rct = 0;
-  int it = 0;
-  double x = 0.0;
-  if (k < a.ntp) x = a.x[k];
-  if (k < a.ntp && !isnan(x)) {
-    double y = a.x[a.ntp + k], z = a.x[2 * a.ntp + k];
-    double vx = a.v[k], vy = a.v[a.ntp + k], vz = a.v[2 * a.ntp + k];
-    const unsigned cmask = a.mask[k];
-    rct = a.n2 * a.absdt * sqrt(vx * vx + vy * vy + vz * vz);
-    double ax, ay, az;
-    tp_kick_acc(a, px0, prc, x, y, z, rct, ax, ay, az);
-    vx += a.h * ax;
-    vy += a.h * ay;
-    vz += a.h * az;
-    x += a.h * P1x / a.m0;
-    y += a.h * P1y / a.m0;
-    z += a.h * P1z / a.m0;
-    xm0 = x;
-    ym0 = y;
-    zm0 = z;
-    vxm = vx;
-    vym = vy;
-    vzm = vz;
-    it = kepler_drift(a.mu, a.dt, x, y, z, vx, vy, vz, a.max_iter);
-    if (it < 0) atomicOr(&a.st->flags, F_KEPLER);
-    atomicAdd(&kh[min(abs(it), kKepBins - 1)], 1u);
-    if (!a.enc_free && cmask) {
-      for (int j = 0; j < a.nm; ++j) {
-        if (!(cmask & (1u << j))) continue;
-        const double4 p0 = ppre[j], q0 = vpre[j], p1 = ppost[j], q1 = vpost[j];
-        const double d2 = hermite_dmin2(a.dt, p0.x - xm0, p0.y - ym0, p0.z - zm0,
-                                        q0.x - vxm, q0.y - vym, q0.z - vzm,
-                                        p1.x - x, p1.y - y, p1.z - z,
-                                        q1.x - vx, q1.y - vy, q1.z - vz);
-        const double rcij = fmax(rct, prc[j]);
-        if (d2 < rcij * rcij) {
-          emask |= 1u << j;
-          a.enc_d2[(size_t)j * a.ntp + k] = d2;
-          a.enc_rc2[(size_t)j * a.ntp + k] = rcij * rcij;
-        }
-      }
-    }
-    if (emask) {
-      listed = true;
+  const double P2x = a.P2[0], P2y = a.P2[1], P2z = a.P2[2];
+  TpListed L;
+  if (k < a.ntp) {
+    if (a.busy[k]) {
+      a.busy[k] = 0;  // still in the last step's refinement: the late pass takes it
     } else {
-      tp_finish(a, pfin, prc, k, x, y, z, vx, vy, vz, rct, P2x, P2y, P2z);
+      const TpPlanets pl = {px0, pfin, ppre, vpre, ppost, vpost, prc};
+      L = tp_particle(a, pl, k, P1x, P1y, P1z, P2x, P2y, P2z, kh);
     }
   }
-  // block-level compaction of the particles with an encounter into this
-  // block's region of the list, and block counters
-  __shared__ int s_cnt[4], s_enc[4], s_kit[4];
+  const bool listed = L.emask != 0u;
+  __shared__ int s_cnt[4], s_enc[4], s_kit[4], s_base;
   const int w = threadIdx.x >> 6;
   const unsigned long long lm = __ballot(listed);
-  int nen = listed ? __popc(emask) : 0;
+  int nen = listed ? __popc(L.emask) : 0;
   for (int o = 32; o > 0; o >>= 1) nen += __shfl_xor(nen, o, 64);
-  const int itm = wave_max_i(abs(it));
+  const int itm = wave_max_i(abs(L.it));
   if (lane == 0) {
     s_cnt[w] = __popcll(lm);
     s_enc[w] = nen;
@@ -239,7 +292,9 @@ __global__ __launch_bounds__(256) void k_tp_main(TpArgs a, const double4* __rest
   for (int q = 0; q < w; ++q) base += s_cnt[q];
   if (threadIdx.x == 0) {
     const int b = blockIdx.x;
-    a.blk_cnt[b] = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+    const int nl = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+    s_base = nl > 0 ? atomicAdd(&a.cnt[0], nl) : 0;
+    a.blk_cnt[b] = nl;
     const int ne = s_enc[0] + s_enc[1] + s_enc[2] + s_enc[3];
     a.blk_enc[b] = ne;
     a.blk_enc_tot[b] += (unsigned long long)ne;
@@ -247,56 +302,56 @@ __global__ __launch_bounds__(256) void k_tp_main(TpArgs a, const double4* __rest
   }
   if (threadIdx.x < kKepBins)
     a.khist[(size_t)blockIdx.x * kKepBins + threadIdx.x] += kh[threadIdx.x];
-  if (listed) {
-    const int64_t pos = (int64_t)blockIdx.x * 256 + base + (int)lanemask_count_tp(lm);
-    a.bs_idx[pos] = (int)k;
-    a.bs_mask[pos] = emask;
-    a.bs_emask[pos] = emask;
-    a.bs_rct[pos] = rct;
-    a.bs_y[pos] = xm0;
-    a.bs_y[a.cap + pos] = ym0;
-    a.bs_y[2 * a.cap + pos] = zm0;
-    a.bs_y[3 * a.cap + pos] = vxm;
-    a.bs_y[4 * a.cap + pos] = vym;
-    a.bs_y[5 * a.cap + pos] = vzm;
-  }
-}
-
-// Exclusive prefix sum of the blocks' list counts (one workgroup of 1024).
-__global__ __launch_bounds__(1024) void k_tp_scan(TpArgs a) {
-  __shared__ int sh[1024];
-  const int t = threadIdx.x;
-  const int64_t chunk = (a.nb + 1023) / 1024;
-  const int64_t lo = min(a.nb, t * chunk), hi = min(a.nb, lo + chunk);
-  int sum = 0;
-  for (int64_t b = lo; b < hi; ++b) sum += a.blk_cnt[b];
-  sh[t] = sum;
   __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const int v = t >= o ? sh[t - o] : 0;
-    __syncthreads();
-    sh[t] += v;
-    __syncthreads();
+  if (listed) {
+    const int at = base + (int)lanemask_count_tp(lm);
+    const int64_t pos = (int64_t)blockIdx.x * 256 + at;
+    tp_list(a, pos, k, L);
+    a.list[s_base + at] = (int)pos;
   }
-  int run = sh[t] - sum;
-  for (int64_t b = lo; b < hi; ++b) {
-    a.blk_off[b] = run;
-    run += a.blk_cnt[b];
-  }
-  if (t == 1023) a.blk_off[a.nb] = sh[1023];
-  if (t == 0) *a.rq_cnt = 0;  // the wave path's queue of this step
 }
 
-// List entry of the d-th listed particle: the block whose region holds it
-// (largest b with blk_off[b] <= d), then the slot inside the region.
-__device__ __forceinline__ int64_t tp_entry(const TpArgs& a, int64_t d) {
-  int64_t lo = 0, hi = a.nb;  // blk_off[lo] <= d < blk_off[hi]
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (a.blk_off[mid] <= d) lo = mid;
-    else hi = mid;
+constexpr int kTpLateLanes = 4;
+
+// The same for the particles that the last step's refinement held (its queue):
+// each takes this step now; one with an encounter is added to its block's
+// region and to lq.  A block's region holds its 256 particles, and the main
+// pass left these out.
+__global__ __launch_bounds__(64) void k_tp_late(TpArgs a, const double4* __restrict__ px0,
+                                                const double4* __restrict__ pfin,
+                                                const double4* __restrict__ ppre,
+                                                const double4* __restrict__ vpre,
+                                                const double4* __restrict__ ppost,
+                                                const double4* __restrict__ vpost,
+                                                const double* __restrict__ prc) {
+  __shared__ unsigned kh[kKepBins];
+  const int nq = *a.prq_cnt;
+  double P1x = 0.0, P1y = 0.0, P1z = 0.0;
+  for (int b = 0; b < a.nblk; ++b) {
+    P1x += a.partP[4 * b + 0];
+    P1y += a.partP[4 * b + 1];
+    P1z += a.partP[4 * b + 2];
   }
-  return lo * 256 + (d - a.blk_off[lo]);
+  const double P2x = a.P2[0], P2y = a.P2[1], P2z = a.P2[2];
+  const TpPlanets pl = {px0, pfin, ppre, vpre, ppost, vpost, prc};
+  // a few particles per wave: the queue is short, and a wave takes every
+  // branch that one of its particles needs
+  if (threadIdx.x >= kTpLateLanes) return;
+  for (int q = blockIdx.x * kTpLateLanes + threadIdx.x; q < nq; q += gridDim.x * kTpLateLanes) {
+    const int64_t k = a.pidx[a.prq[q]];
+    const TpListed L = tp_particle(a, pl, k, P1x, P1y, P1z, P2x, P2y, P2z, kh);
+    if (L.it == 0) continue;  // removed in that refinement
+    const int64_t b = k >> 8;
+    atomicMax(&a.blk_kit[b], abs(L.it));
+    atomicAdd(&a.khist[(size_t)b * kKepBins + min(abs(L.it), kKepBins - 1)], 1ull);
+    if (!L.emask) continue;
+    const int ne = __popc(L.emask);
+    atomicAdd(&a.blk_enc[b], ne);
+    atomicAdd(&a.blk_enc_tot[b], (unsigned long long)ne);
+    const int64_t pos = b * 256 + atomicAdd(&a.blk_cnt[b], 1);
+    tp_list(a, pos, k, L);
+    a.lq[atomicAdd(&a.cnt[1], 1)] = (int)pos;
+  }
 }
 
 // One wave per listed particle: its group is the particle (member 0) and the
@@ -346,7 +401,7 @@ __device__ void tp_remove(const TpArgs& a, int64_t e, unsigned em, int cb, long 
   if ((int64_t)slot < a.ntp) {
     CollRec r;
     r.tp = k;
-    r.step = (long long)a.st->nstep - 1;
+    r.step = (long long)*a.nstep - 1;
     r.planet = __ffs(mm2) - 1;
     r.pad = 0;
     r.frac = ldexp((double)cpos, -a.max_depth);
@@ -453,6 +508,21 @@ __device__ void tp_plan(const TpArgs& a) {
   }
 }
 
+// The planets of the step into its slot, from the main-mode arrays that their
+// next step overwrites.
+__device__ void tp_snap(const TpArgs& a, const TpSlot& q) {
+  const int t = threadIdx.x;
+  if (t < a.nm) {
+    q.px0[t] = a.px0[t];
+    q.ppre[t] = a.ppre[t];
+    q.vpre[t] = a.vpre[t];
+    q.pfin[t] = a.pfin[t];
+    q.rc[t] = a.rc[t];
+  }
+  if (t < 3) q.P2[t] = a.P2[t];
+  if (t == 3) *q.nstep = *a.nstep;
+}
+
 // Particle derivative in its group with planet position (qx, qy, qz).
 struct PairK {
   double Gm, rcij, i09, near2;  // near2: rc_ij^2 (1 + 1e-12), 0 when rc_ij = 0
@@ -487,9 +557,11 @@ __device__ __forceinline__ void tp_pair_acc(double Gm0, const PairK& Q, double x
 // relative change, and the planet's own, are within tolerance is taken.
 // Passages that need refinement or meet several planets are queued for the
 // wave path (one atomic per wave), which spreads them evenly over its waves.
-__global__ __launch_bounds__(256) void k_tp_bs1(TpArgs a) {
-  const int64_t nl = a.blk_off[a.nb];
-  const double P2x = a.st->P2[0], P2y = a.st->P2[1], P2z = a.st->P2[2];
+// late: the passages of lq instead of list.
+__global__ __launch_bounds__(256) void k_tp_bs1(TpArgs a, int late) {
+  const int64_t nl = a.cnt[late];
+  const int* __restrict__ list = late ? a.lq : a.list;
+  const double P2x = a.P2[0], P2y = a.P2[1], P2z = a.P2[2];
   unsigned long long nsub = 0;
   const int lane = threadIdx.x & 63;
   const int c = lane & 7;  // column of this lane
@@ -504,7 +576,7 @@ __global__ __launch_bounds__(256) void k_tp_bs1(TpArgs a) {
   }
   const int64_t stride = (int64_t)gridDim.x * 256 / 8;
   for (int64_t d = ((int64_t)blockIdx.x * 256 + threadIdx.x) / 8; d < nl; d += stride) {
-    const int64_t e = tp_entry(a, d);
+    const int64_t e = list[d];
     const unsigned em = a.bs_mask[e];
     bool wave = true;  // left to the wave path
     if (__popc(em) == 1) {
@@ -617,9 +689,12 @@ __global__ __launch_bounds__(256) void k_tp_bs1(TpArgs a) {
     if (qm) {
       const int leader = __ffsll((long long)qm) - 1;
       int base = 0;
-      if (lane == leader) base = atomicAdd(a.rq_cnt, __popcll(qm));
+      if (lane == leader) base = atomicAdd(&a.cnt[2], __popcll(qm));
       base = __shfl(base, leader, 64);
-      if (q0) a.rq[base + (int)lanemask_count_tp(qm)] = e;
+      if (q0) {
+        a.rq[base + (int)lanemask_count_tp(qm)] = (int)e;
+        if (a.defer) a.busy[a.bs_idx[e]] = 1;
+      }
     }
   }
   for (int o = 32; o > 0; o >>= 1) nsub += __shfl_xor(nsub, o, 64);
@@ -629,13 +704,20 @@ __global__ __launch_bounds__(256) void k_tp_bs1(TpArgs a) {
   if (threadIdx.x == 0) a.sub[blockIdx.x] += s_sub[0] + s_sub[1] + s_sub[2] + s_sub[3];
 }
 
-__global__ __launch_bounds__(64) void k_tp_bs(TpArgs a) {
-  __shared__ double mm[kBsPar], mrc[kBsPar];
-  const int lane = threadIdx.x;
-  const int nq = *a.rq_cnt;
+// One wave per queued particle, four to a workgroup: a few hundred passages
+// then sit on half of the compute units and leave the others, and half of
+// their own registers, to the next step's kernels that run beside them (one
+// to a workgroup they sat on nearly all, and the planets' pair kernel, 16
+// waves on one unit, waited 20 us a step for one without any).
+__global__ __launch_bounds__(64 * kTpBsWaves, 2) void k_tp_bs(TpArgs a) {
+  __shared__ double s_mm[kTpBsWaves][kBsPar], s_mrc[kTpBsWaves][kBsPar];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double *mm = s_mm[w], *mrc = s_mrc[w];
+  const int slot = blockIdx.x * kTpBsWaves + w;
+  const int nq = a.cnt[2];
   long long nsub = 0;
-  const double P2x = a.st->P2[0], P2y = a.st->P2[1], P2z = a.st->P2[2];
-  for (int q = blockIdx.x; q < nq; q += gridDim.x) {
+  const double P2x = a.P2[0], P2y = a.P2[1], P2z = a.P2[2];
+  for (int q = slot; q < nq; q += kTpBsGrid) {
     const int64_t e = a.rq[q];
     const unsigned em = a.bs_mask[e];
     if (em == 0u) continue;  // finished by the whole-step attempt
@@ -645,7 +727,7 @@ __global__ __launch_bounds__(64) void k_tp_bs(TpArgs a) {
       if (lane == 0) atomicOr(&a.st->flags, F_GROUP);
       continue;
     }
-    __syncthreads();
+    wsync();
     if (lane == 0) {
       mm[0] = 0.0;
       mrc[0] = rct;
@@ -657,7 +739,7 @@ __global__ __launch_bounds__(64) void k_tp_bs(TpArgs a) {
         mrc[t] = a.rc[j];
       }
     }
-    __syncthreads();
+    wsync();
     double y[6];
     const double rtp = a.rad[kTpMaxPlanets + a.bs_idx[e]];
     int r, cb = 0;
@@ -676,7 +758,7 @@ __global__ __launch_bounds__(64) void k_tp_bs(TpArgs a) {
                 P2z);
     }
   }
-  if (lane == 0 && nsub > 0) a.sub[kTpBs1Grid + blockIdx.x] += (unsigned long long)nsub;
+  if (lane == 0 && nsub > 0) a.sub[kTpBs1Grid + slot] += (unsigned long long)nsub;
 }
 
 // Rows [nm, nm + ntp) of the caller's n x 3 arrays into SoA; heliocentric
@@ -770,39 +852,53 @@ __global__ void k_tp_radii(const double* __restrict__ r, double* __restrict__ ra
   }
 }
 
-TpArgs tp_args(const MassiveWs& w, const TpWs& t, const StepConsts& c) {
+// Arguments of step k of a graph, with the lists of parity k & 1.  slot: the
+// planets of the step as its main pass left them in slot k (the refinement,
+// beside which their next step runs); otherwise as the main-mode arrays hold
+// them.
+TpArgs tp_args(const MassiveWs& w, const TpWs& t, const StepConsts& c, int k, bool slot) {
+  const TpLists &l = t.lists[k & 1], &pl = t.lists[(k & 1) ^ 1];
+  const TpSlot& sl = t.slot[k];
   TpArgs a;
   a.x = t.x;
   a.v = t.v;
   a.mask = t.mask;
-  a.px0 = w.xstart;
-  a.ppre = w.xpre;
-  a.vpre = w.vpre;
+  a.px0 = slot ? sl.px0 : w.xstart;
+  a.ppre = slot ? sl.ppre : w.xpre;
+  a.vpre = slot ? sl.vpre : w.vpre;
   a.ppost = w.xpost;
   a.vpost = w.vpost;
-  a.pfin = w.xs;
-  a.rc = w.rc_cur;
+  a.pfin = slot ? sl.pfin : w.xs;
+  a.rc = slot ? sl.rc : w.rc_cur;
   a.partP = w.partP;
+  a.P2 = slot ? sl.P2 : w.st->P2;
+  a.nstep = slot ? sl.nstep : &w.st->nstep;
   a.st = w.st;
-  a.bs_idx = t.bs_idx;
-  a.bs_mask = t.bs_mask;
-  a.bs_emask = t.bs_emask;
+  a.bs_idx = l.idx;
+  a.bs_mask = l.mask;
+  a.bs_emask = l.emask;
   a.enc_d2 = t.enc_d2;
   a.enc_rc2 = t.enc_rc2;
-  a.bs_rct = t.bs_rct;
-  a.bs_y = t.bs_y;
+  a.bs_rct = l.rct;
+  a.bs_y = l.y;
   a.rad = t.rad;
   a.coll = t.coll;
   a.blk_cnt = t.blk_cnt;
-  a.blk_off = t.blk_off;
   a.blk_enc = t.blk_enc;
   a.blk_enc_tot = t.blk_enc_tot;
   a.blk_kit = t.blk_kit;
   a.khist = t.khist;
   a.sub = t.sub;
-  a.pl = t.pl;
-  a.rq = t.rq;
-  a.rq_cnt = t.rq_cnt;
+  a.pl = sl.pl;
+  a.list = l.list;
+  a.lq = l.lq;
+  a.rq = l.rq;
+  a.cnt = sl.cnt;
+  a.prq = pl.rq;
+  a.prq_cnt = k > 0 ? t.slot[k - 1].cnt + 2 : nullptr;
+  a.pidx = pl.idx;
+  a.busy = t.busy;
+  a.defer = 0;
   a.ntp = t.ntp;
   a.cap = t.cap;
   a.nb = t.nb;
@@ -841,17 +937,33 @@ size_t tp_carve(TpWs& t, int64_t ntp, int nm, void* base) {
   t.x = (double*)take(3 * n * sizeof(double));
   t.v = (double*)take(3 * n * sizeof(double));
   t.mask = (unsigned*)take(n * sizeof(unsigned));
-  t.bs_idx = (int*)take(nc * sizeof(int));
-  t.bs_mask = (unsigned*)take(nc * sizeof(unsigned));
-  t.bs_emask = (unsigned*)take(nc * sizeof(unsigned));
+  for (TpLists& l : t.lists) {
+    l.idx = (int*)take(nc * sizeof(int));
+    l.mask = (unsigned*)take(nc * sizeof(unsigned));
+    l.emask = (unsigned*)take(nc * sizeof(unsigned));
+    l.rct = (double*)take(nc * sizeof(double));
+    l.y = (double*)take(6 * nc * sizeof(double));
+    l.list = (int*)take(nc * sizeof(int));
+    l.lq = (int*)take(nc * sizeof(int));
+    l.rq = (int*)take(nc * sizeof(int));
+  }
+  for (TpSlot& q : t.slot) {
+    constexpr size_t np = kTpMaxPlanets;
+    q.px0 = (double4*)take(np * sizeof(double4));
+    q.ppre = (double4*)take(np * sizeof(double4));
+    q.vpre = (double4*)take(np * sizeof(double4));
+    q.pfin = (double4*)take(np * sizeof(double4));
+    q.rc = (double*)take(np * sizeof(double));
+    q.P2 = (double*)take(3 * sizeof(double));
+    q.nstep = (unsigned long long*)take(sizeof(unsigned long long));
+    q.cnt = (int*)take(3 * sizeof(int));
+    q.pl = (double*)take(np * kPlStride * sizeof(double));
+  }
   t.enc_d2 = (double*)take((size_t)nm * n * sizeof(double));
   t.enc_rc2 = (double*)take((size_t)nm * n * sizeof(double));
-  t.bs_rct = (double*)take(nc * sizeof(double));
-  t.bs_y = (double*)take(6 * nc * sizeof(double));
   t.rad = (double*)take((kTpMaxPlanets + n) * sizeof(double));
   t.coll = (CollRec*)take(n * sizeof(CollRec));
   t.blk_cnt = (int*)take(nb * sizeof(int));
-  t.blk_off = (int*)take((nb + 1) * sizeof(int));
   t.blk_enc = (int*)take(nb * sizeof(int));
   // cumulative counters, cleared at init: enc totals, Kepler maxima, substeps
   t.cum = base ? (char*)base + off : nullptr;
@@ -860,10 +972,8 @@ size_t tp_carve(TpWs& t, int64_t ntp, int nm, void* base) {
   t.blk_kit = (int*)take(nb * sizeof(int));
   t.khist = (unsigned long long*)take(nb * kKepBins * sizeof(unsigned long long));
   t.sub = (unsigned long long*)take(kTpSubSlots * sizeof(unsigned long long));
+  t.busy = (unsigned char*)take(n);
   t.cum_bytes = off - cum0;
-  t.pl = (double*)take((size_t)kTpMaxPlanets * kPlStride * sizeof(double));
-  t.rq = (int64_t*)take(nc * sizeof(int64_t));
-  t.rq_cnt = (int*)take(sizeof(int));
   return off;
 }
 
@@ -910,9 +1020,9 @@ hipError_t tp_read_encounters(const TpWs& t, std::vector<TpEnc>* out, hipStream_
   std::vector<double> d2((size_t)t.nm * t.ntp), rc2((size_t)t.nm * t.ntp);
   hipError_t e = hipMemcpyAsync(cnt.data(), t.blk_cnt, t.nb * sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(idx.data(), t.bs_idx, t.cap * sizeof(int), hipMemcpyDeviceToHost, s);
+    e = hipMemcpyAsync(idx.data(), t.lists[t.last].idx, t.cap * sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(em.data(), t.bs_emask, t.cap * sizeof(unsigned), hipMemcpyDeviceToHost, s);
+    e = hipMemcpyAsync(em.data(), t.lists[t.last].emask, t.cap * sizeof(unsigned), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess)
     e = hipMemcpyAsync(d2.data(), t.enc_d2, d2.size() * sizeof(double), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess)
@@ -966,24 +1076,43 @@ hipError_t tp_unpack(const MassiveWs& w, const TpWs& t, const StepConsts& c, dou
 
 hipError_t tp_prime(const MassiveWs& w, const TpWs& t, const StepConsts& c, hipStream_t s) {
   if (t.ntp <= 0) return hipSuccess;
-  TpArgs a = tp_args(w, t, c);
+  TpArgs a = tp_args(w, t, c, 0, false);
   hipLaunchKernelGGL(k_tp_prime, dim3(ceil_div64(t.ntp, 256)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t tp_step(const MassiveWs& w, const TpWs& t, const StepConsts& c, hipStream_t s) {
+#define TP_PLANETS(a)                                                                    \
+  (const double4*)(a).px0, (const double4*)(a).pfin, (const double4*)(a).ppre,           \
+      (const double4*)(a).vpre, (const double4*)(a).ppost, (const double4*)(a).vpost,    \
+      (const double*)(a).rc
+
+hipError_t tp_main(const MassiveWs& w, const TpWs& t, const StepConsts& c, int k, bool defer,
+                   hipStream_t s) {
   if (t.ntp <= 0) return hipSuccess;
-  TpArgs a = tp_args(w, t, c);
-  // with encounters, one block more: the planets' whole-step table
-  hipLaunchKernelGGL(k_tp_main, dim3((unsigned)(t.nb + (c.encounter_free ? 0 : 1))), dim3(256), 0, s, a,
-                     (const double4*)a.px0, (const double4*)a.pfin, (const double4*)a.ppre,
-                     (const double4*)a.vpre, (const double4*)a.ppost, (const double4*)a.vpost,
-                     (const double*)a.rc);
-  if (!c.encounter_free) {
-    hipLaunchKernelGGL(k_tp_scan, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(k_tp_bs1, dim3(kTpBs1Grid), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_tp_bs, dim3(kTpBsGrid), dim3(64), 0, s, a);
-  }
+  TpArgs a = tp_args(w, t, c, k, false);
+  a.defer = defer;
+  // with encounters, one block more: the planets' slot and whole-step table
+  const unsigned nb = (unsigned)(t.nb + (c.encounter_free ? 0 : 1));
+  hipLaunchKernelGGL(k_tp_main, dim3(nb), dim3(256), 0, s, a, t.slot[k], TP_PLANETS(a));
+  if (!c.encounter_free) hipLaunchKernelGGL(k_tp_bs1, dim3(kTpBs1Grid), dim3(256), 0, s, a, 0);
+  return hipGetLastError();
+}
+
+hipError_t tp_late(const MassiveWs& w, const TpWs& t, const StepConsts& c, int k, bool defer,
+                   hipStream_t s) {
+  if (t.ntp <= 0 || c.encounter_free) return hipSuccess;
+  TpArgs a = tp_args(w, t, c, k, false);
+  a.defer = defer;
+  hipLaunchKernelGGL(k_tp_late, dim3(kTpLateGrid), dim3(64), 0, s, a, TP_PLANETS(a));
+  hipLaunchKernelGGL(k_tp_bs1, dim3(kTpLateGrid), dim3(256), 0, s, a, 1);
+  return hipGetLastError();
+}
+
+hipError_t tp_refine(const MassiveWs& w, const TpWs& t, const StepConsts& c, int k,
+                     hipStream_t s) {
+  if (t.ntp <= 0 || c.encounter_free) return hipSuccess;
+  hipLaunchKernelGGL(k_tp_bs, dim3(kTpBsGrid / kTpBsWaves), dim3(64 * kTpBsWaves), 0, s,
+                     tp_args(w, t, c, k, true));
   return hipGetLastError();
 }
 
