@@ -665,7 +665,6 @@ struct EncArgs {
   double dt;
 };
 
-constexpr int kEncThreads = 1024;
 
 // Exclusive scan over a block of NT threads; returns the prefix and puts the
 // total in *total.
@@ -732,18 +731,21 @@ __global__ __launch_bounds__(kVecBlock) void k_encounter(EncArgs a) {
 }
 
 // Encounter search over every pair i < j (the composed steps, Sec. 2.3: no
-// prechecker).  Workgroup (ti, tj), tj >= ti, takes i in tile ti and j in
-// tile tj (64 bodies each); the j tile's states before and after the drift
-// and radii sit in LDS; lane l serves i = 64 ti + l over the 16 partners of
-// its quarter, and confirmed pairs are appended as in k_encounter.
-constexpr int kEncTile = 64;
+// prechecker).  Workgroup (ti, cj) takes i in tile ti (64 bodies) and j in
+// chunk cj (16 bodies), j > i somewhere; the chunk's states before and after
+// the drift and radii sit in LDS; lane l serves i = 64 ti + l over its wave's 4
+// partners, and confirmed pairs are appended as in k_encounter.  A Hermite test
+// is a chain of ~60 operations with a root and two divisions, so a few
+// hundred bodies are bound by its length: 64 partners per workgroup, 16 in turn
+// per lane, took 10.4 us at 300 bodies, 4 take 4.7 us.
+constexpr int kEncTile = 64, kEncChunk = 16;
 __global__ __launch_bounds__(256) void k_encounter_all(EncArgs a) {
-  __shared__ double sj[13][kEncTile];
-  const int ti = blockIdx.x, tj = blockIdx.y;
-  if (tj < ti) return;  // upper triangle of tiles (uniform over the workgroup)
+  __shared__ double sj[13][kEncChunk];
+  const int ti = blockIdx.x, j0 = blockIdx.y * kEncChunk;
+  if (j0 + kEncChunk - 1 <= ti * kEncTile) return;  // no j > i (uniform over the workgroup)
   const int tid = threadIdx.x, lane = tid & 63, q = tid >> 6;
-  if (tid < kEncTile) {
-    const int j = tj * kEncTile + tid;
+  if (tid < kEncChunk) {
+    const int j = j0 + tid;
     double4 p0 = make_double4(0, 0, 0, 0), v0 = p0, p1 = p0, v1 = p0;
     double rc = 0.0;
     if (j < a.n) {
@@ -767,7 +769,6 @@ __global__ __launch_bounds__(256) void k_encounter_all(EncArgs a) {
     sj[11][tid] = v1.z;
     sj[12][tid] = rc;
   }
-  __syncthreads();
   const int i = ti * kEncTile + lane;
   const bool iv = i < a.n;
   double4 xi0 = make_double4(0, 0, 0, 0), vi0 = xi0, xi1 = xi0, vi1 = xi0;
@@ -779,9 +780,11 @@ __global__ __launch_bounds__(256) void k_encounter_all(EncArgs a) {
     vi1 = a.vv[i];
     rci = a.rc[i];
   }
-  for (int t = 0; t < kEncTile / 4; ++t) {
-    const int k = q * (kEncTile / 4) + t;
-    const int j = tj * kEncTile + k;
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < kEncChunk / 4; ++t) {
+    const int k = q * (kEncChunk / 4) + t;
+    const int j = j0 + k;
     bool enc = false;
     double d2 = 0.0, rc2 = 0.0;
     if (iv && j < a.n && j > i) {
@@ -995,13 +998,6 @@ __device__ __forceinline__ int group_phase(const EncArgs& a, int ne_all, GL& L,
   return ng;
 }
 
-__global__ __launch_bounds__(kEncThreads) void k_group(EncArgs a) {
-  __shared__ GroupLds<kEncThreads, kGroupMaxN, kEncLds> L;
-  if (a.st->flags & F_NMIN) return;  // the run stopped below nmin bodies
-  (void)group_phase<kEncThreads>(a, a.st->nenc, L, nullptr, true);
-}
-
-
 // ---------------------------------------------------------------------------
 struct BsArgs {
   double4* __restrict__ xm;
@@ -1026,8 +1022,7 @@ struct BsArgs {
   int max_depth, coll, ev_cap;
 };
 
-// The BS kernels (k_group_bs, and k_bs for the composed steps) run kBsWaves
-// waves per workgroup.  Groups of up to kBsPar members
+// The BS kernel (k_group_bs) runs kBsWaves waves per workgroup.  Groups of up to kBsPar members
 // without collisions take all of them (speculative depths spread over the
 // waves); every other group is integrated by wave 0 alone while the others
 // wait at the group's closing barrier.  The lanes of that one wave order
@@ -1684,14 +1679,6 @@ __device__ __forceinline__ void bs_groups(const BsArgs& a, int ng, const int* go
     __syncthreads();
   }
   if (threadIdx.x == 0 && nsub > 0) atomicAdd(&a.st->bs_sub, (unsigned long long)nsub);
-}
-
-// BS of the groups that the grouping kernel left in global memory.
-__global__ __launch_bounds__(64 * kBsWaves) void k_bs(BsArgs a) {
-  __shared__ BsLds L;
-  if (a.st->flags & F_NMIN) return;  // the run stopped below nmin bodies
-  const int ng = __builtin_amdgcn_readfirstlane(a.st->ngroups);
-  bs_groups(a, ng, a.goff, a.gmem, L);
 }
 
 // Grouping (App. A) and BS (Sec. 3.2.6) in one launch: every workgroup
@@ -2506,12 +2493,11 @@ hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
     b.ev_cap = w.ev_cap;
     const dim3 bs_grid(std::max(1, std::min(256, w.n / 2)));
     if (c.all_pairs) {
-      // composed steps (not timed per kernel): every pair tested, then the
-      // grouping and BS on their own
-      const int nt = ceil_div(w.n, kEncTile);
-      hipLaunchKernelGGL(k_encounter_all, dim3(nt, nt), dim3(256), 0, s, e);
-      hipLaunchKernelGGL(k_group, dim3(1), dim3(kEncThreads), 0, s, e);
-      hipLaunchKernelGGL(k_bs, bs_grid, dim3(64 * kBsWaves), 0, s, b);
+      // composed steps (not timed per kernel): every pair tested
+      hipLaunchKernelGGL(k_encounter_all, dim3(ceil_div(w.n, kEncTile), ceil_div(w.n, kEncChunk)),
+                         dim3(256), 0, s, e);
+      hipLaunchKernelGGL((k_group_bs<1, kGroupMaxN, kEncLds>), bs_grid, dim3(64 * kBsWaves), 0, s,
+                         e, b);
     } else {
       STEP_LAUNCH(1, k_encounter, dim3(ceil_div(w.n * w.cpb, kVecBlock)), dim3(kVecBlock), e);
       const auto kgb = tpcnt ? k_group_bs<2, kTpMaxPlanets, 512> : k_group_bs<1, kGroupMaxN, kEncLds>;

@@ -109,3 +109,25 @@ def test_composed_order_limits():
     with pytest.raises(G.GengaError):
         G.TestParticleSimulation(planets.m, planets.x, planets.u, xt, ut,
                                  G.default_params(order=4))
+
+
+# the all-pairs encounter search at the edges of its tiles (64) and chunks (16),
+# bodies packed so that most pairs meet; encounter counts must agree
+@pytest.mark.parametrize("n", [2, 15, 16, 17, 63, 64, 65, 81, 129])
+def test_composed_encounter_tiles(n):
+    print("order 4 tiles n", n, flush=True)
+    rng = np.random.default_rng(70 + n)
+    m = np.full(n, 1e-10)
+    a = 1.0 + 1e-3 * np.arange(n)
+    lam = 0.02 * np.arange(n)
+    x, u = W.elements_to_cartesian(1.0 + m, a, np.full(n, 1e-3), rng.uniform(0, 0.01, n),
+                                   np.zeros(n), np.zeros(n), lam)
+    gp = G.default_params(order=4)
+    sim = G.Simulation(m, x, u, gp, coords="helio")
+    sim.step(1)
+    sim.check()
+    xg, vg = (t.cpu().numpy() for t in sim.state("dem"))
+    v0 = O.helio_to_dem(_op(gp), m, u)
+    xo, vo, _, st = O.step_order(_op(gp), 4, m, x, v0, 1)
+    assert sim.stats()["enc_total"] == st["enc_total"] > 0
+    assert _rel(xg, xo) < 1e-12 and _rel(vg, vo) < 1e-12
