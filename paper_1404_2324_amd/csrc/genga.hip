@@ -1055,7 +1055,7 @@ size_t genga_adj_buffer_bytes(genga_ctx* ctx, int64_t nsteps, int ckpt_every) {
   if (!adj_ok(ctx) || nsteps < 1 || nsteps > INT_MAX || ckpt_every < 1) return 0;
   const int K = (int)std::min<int64_t>(ckpt_every, nsteps);
   if (adj_hybrid(ctx))
-    return adj_ckpt_bytes(ctx, nsteps, ckpt_every) + hadj_work_bytes(ctx->b.nsys, K);
+    return adj_ckpt_bytes(ctx, nsteps, ckpt_every) + hadj_work_bytes(ctx->b.nsys, ctx->b.nb, K);
   return adj_ckpt_bytes(ctx, nsteps, ckpt_every) + adj_tape_bytes(ctx->b.nb, K);
 }
 

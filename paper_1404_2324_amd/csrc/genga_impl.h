@@ -367,7 +367,7 @@ bool batch_variant_ok(const BatchWs& b, int v);
 // hybrid adjoint (hadj.hip): checkpoints of T steps every K, and the backward
 // pass's workspace (tape of a segment, BS substep starts, Gragg positions)
 size_t hadj_ckpt_bytes(int64_t nb, int T, int K);
-size_t hadj_work_bytes(int nsys, int K);
+size_t hadj_work_bytes(int nsys, int64_t nb, int K);
 hipError_t hadj_forward(const BatchWs& b, const StepConsts& c, int T, int K, double* ckpt,
                         hipStream_t s);
 hipError_t hadj_backward(const BatchWs& b, const StepConsts& c, int T, int K, double* ckpt,

@@ -22,15 +22,18 @@
 // side by side (lane 8 c + q: column c of member slot q), larger groups one
 // column after another.  Forward: the state and the candidate set every k
 // steps.  Backward, per segment from the last: the segment replayed keeping
-// each step's start (the tape), then per step in reverse the step
-// recomputed and its pieces reversed:
+// each step's intermediate values (the tape) and its groups' accepted BS
+// substeps (a pool; recomputing both per step in reverse took 3290 us instead of
+// 1610 us for 16 steps of 256 systems of 8), then per step in reverse its pieces
+// reversed.  Bound by the chain of the system with the most BS work: one wave
+// per system, its divisions and roots (div_nr, sqrt_nr: 800 -> 650 us forward).
 //   kick   v' = v + h a_B(x; m, rc):  x^ += A^T (h v'^), with the mass and
 //          radius adjoints; for a pair term G m_j f(r, rc) d, d = x_j - x_i,
 //          f = K/r^3 - K'/r^2, the lane's share is
 //          G [f u + (f_r / r)(d.u) d], u = m_i w_j - m_j w_i
 //   Sun    x' = x + h P(v)/m0
 //   drift  the Kepler VJP (implicit function for the universal anomaly)
-//   BS     the group's BS rerun keeping the start of each accepted substep;
+//   BS     from the start of each accepted substep:
 //          an accepted substep's value is a fixed linear combination
 //          sum_q W_q G_q of the Gragg results of its columns (the
 //          Aitken-Neville tableau is linear in them), so its adjoint is
@@ -47,6 +50,8 @@ namespace {
 
 constexpr int kHK = 8;              // BS columns, n_k = 2k substeps
 constexpr int kHLeaf = 64;          // accepted BS substeps of one group in one step
+constexpr int kHPool = 64;          // those kept from a segment's replay, all groups and steps
+constexpr int kHTape = 21;          // values kept of a body and step
 constexpr int kHPos = 2 * kHK + 1;  // positions of the longest Gragg sequence
 
 // Aitken-Neville weights: an attempt that stops at column kk (0-based)
@@ -78,8 +83,8 @@ struct HArgs {
   const int* __restrict__ off;
   const double* __restrict__ m0;
   double* __restrict__ ckpt;  // [C][7][nb]: x, y, z, vx, vy, vz, candidate bits
-  double* __restrict__ tape;  // [K][7][nl]
-  double* __restrict__ leaf;  // [kHLeaf][6][nl]: starts of accepted BS substeps
+  double* __restrict__ tape;  // [K][kHTape][nb]: the steps' intermediate values (StepVals)
+  double* __restrict__ leaf;  // [kHPool + kHLeaf][6][nb]: starts of accepted BS substeps
   double* __restrict__ zpos;  // [kHPos][3][nl]: positions of one Gragg sequence
   const double* __restrict__ gxT;
   const double* __restrict__ gvT;
@@ -110,16 +115,17 @@ __device__ __forceinline__ unsigned long long readlane_u64(unsigned long long v,
 // Changeover of Eqs. (4)-(5) for a pair at r with pair radius rc:
 // y = (r - 0.1 rc)/(0.9 rc), K = y^2/D, D = 2y^2 - 2y + 1, and dK/dr.  The
 // forward map rounds like the plain definitions (divisions and square roots
-// correctly rounded, no fused multiply-adds: this file is built with
-// -ffp-contract=off), so that its close encounters follow the reference
-// trajectory as closely as rounding allows.
+// correctly rounded, by div_nr and sqrt_nr where their operands allow; no other
+// fused multiply-adds: this file is built with -ffp-contract=off), so that its
+// close encounters follow the reference trajectory as closely as rounding
+// allows.
 __device__ __forceinline__ void chg(double r, double rc, double& K, double& Kr) {
   if (!(rc > 0.0)) {
     K = 1.0;
     Kr = 0.0;
     return;
   }
-  const double y = (r - 0.1 * rc) / (0.9 * rc);
+  const double y = div_nr(r - 0.1 * rc, 0.9 * rc);
   if (y <= 0.0) {
     K = 0.0;
     Kr = 0.0;
@@ -128,8 +134,8 @@ __device__ __forceinline__ void chg(double r, double rc, double& K, double& Kr) 
     Kr = 0.0;
   } else {
     const double D = 2.0 * y * y - 2.0 * y + 1.0;
-    K = y * y / D;
-    Kr = 2.0 * y * (1.0 - y) / (D * D) / (0.9 * rc);
+    K = div_nr(y * y, D);
+    Kr = div_nr(div_nr(2.0 * y * (1.0 - y), D * D), 0.9 * rc);
   }
 }
 
@@ -176,11 +182,11 @@ __device__ __forceinline__ void accel_B(const HArgs& a, const Sys& S, const doub
     if (S.act && j != S.lane) {
       const double d0 = xj - x[0], d1 = yj - x[1], d2 = zj - x[2];
       const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-      const double r = sqrt(r2);
+      const double r = sqrt_nr(r2);
       const double rcij = rc > rcj ? rc : rcj;
       double K, dK;
       chg(r, rcij, K, dK);
-      const double f = K / (r2 * r) - dK / r2;
+      const double f = div_nr(K, r2 * r) - div_nr(dK, r2);
       const double s = a.G * mj * f;
       acc[0] += s * d0;
       acc[1] += s * d1;
@@ -214,8 +220,8 @@ __device__ __forceinline__ void lane_sum3(const Sys& S, const double w[3], doubl
 __device__ __forceinline__ void ha_deriv(const HArgs& a, const Sys& S, unsigned long long M, bool mem, double rc,
                          const double y[6], double dy[6]) {
   const double r2 = y[0] * y[0] + y[1] * y[1] + y[2] * y[2];
-  const double r = sqrt(r2);
-  const double fs = -S.Gm0 / (r2 * r);
+  const double r = sqrt_nr(r2);
+  const double fs = div_nr(-S.Gm0, r2 * r);
   double a0 = fs * y[0], a1 = fs * y[1], a2 = fs * y[2];
   for (unsigned long long q = M; q; q &= q - 1) {
     const int j = __builtin_ctzll(q);
@@ -224,11 +230,11 @@ __device__ __forceinline__ void ha_deriv(const HArgs& a, const Sys& S, unsigned 
     if (mem && j != S.lane) {
       const double d0 = xj - y[0], d1 = yj - y[1], d2 = zj - y[2];
       const double q2 = d0 * d0 + d1 * d1 + d2 * d2;
-      const double qq = sqrt(q2);
+      const double qq = sqrt_nr(q2);
       const double rcij = rc > rcj ? rc : rcj;
       double K, dK;
       chg(qq, rcij, K, dK);
-      const double f = (1.0 - K) / (q2 * qq) + dK / q2;
+      const double f = div_nr(1.0 - K, q2 * qq) + div_nr(dK, q2);
       const double sj = a.G * mj * f;
       a0 += sj * d0;
       a1 += sj * d1;
@@ -391,8 +397,8 @@ __device__ __forceinline__ Par par_of(const Sys& S, unsigned long long M, double
 __device__ __forceinline__ void ha_deriv_par(const HArgs& a, const Sys& S, const Par& P,
                                              const double y[6], double dy[6]) {
   const double r2 = y[0] * y[0] + y[1] * y[1] + y[2] * y[2];
-  const double r = sqrt(r2);
-  const double fs = -S.Gm0 / (r2 * r);
+  const double r = sqrt_nr(r2);
+  const double fs = div_nr(-S.Gm0, r2 * r);
   double a0 = fs * y[0], a1 = fs * y[1], a2 = fs * y[2];
   const int base = (S.lane & ~7) + P.s * P.w;
 #pragma unroll
@@ -403,11 +409,11 @@ __device__ __forceinline__ void ha_deriv_par(const HArgs& a, const Sys& S, const
     if (t < P.sz && P.on && t != P.q) {
       const double d0 = xj - y[0], d1 = yj - y[1], d2 = zj - y[2];
       const double q2 = d0 * d0 + d1 * d1 + d2 * d2;
-      const double qq = sqrt(q2);
+      const double qq = sqrt_nr(q2);
       const double rcij = P.rc > P.prc[t] ? P.rc : P.prc[t];
       double K, dK;
       chg(qq, rcij, K, dK);
-      const double f = (1.0 - K) / (q2 * qq) + dK / q2;
+      const double f = div_nr(1.0 - K, q2 * qq) + div_nr(dK, q2);
       const double sj = a.G * P.pm[t] * f;
       a0 += sj * d0;
       a1 += sj * d1;
@@ -578,12 +584,12 @@ __device__ __forceinline__ int bs_attempt_par(const HArgs& a, const Sys& S,
 
 // BS of one group over tau with binary refinement (as the main mode): y is
 // the members' state in and out.  With REC the start of every accepted
-// substep goes to the lane's leaf slots and its length and column to lh, lk
-// (LDS).  Returns 0, or -1 when the depth is exhausted; *nleaf counts the
-// accepted substeps.
+// substep goes to the bodies' leaf slots from l0 on and its length and column
+// to lh, lk (LDS), up to `room` of them.  Returns 0, or -1 when the depth is
+// exhausted; *nleaf counts the accepted substeps.
 template <bool REC>
 __device__ __forceinline__ int bs_group(const HArgs& a, const Sys& S, unsigned long long M, bool mem, double rc,
-                        double y[6], double* lh, int* lk, int* nleaf) {
+                        double y[6], double* lh, int* lk, int* nleaf, int l0 = 0, int room = 0) {
   const Par P = par_of(S, M, rc, true);
   const int D = a.bs_depth;
   const int64_t total = (int64_t)1 << D;
@@ -601,12 +607,14 @@ __device__ __forceinline__ int bs_group(const HArgs& a, const Sys& S, unsigned l
       d += sa;
       const double hh = ldexp(a.dt, -d);  // the accepted substep's length
       if (REC) {
-        if (nl < kHLeaf) {
+        if (nl < room) {
+          if (mem) {
 #pragma unroll
-          for (int c = 0; c < 6; ++c) a.leaf[((size_t)nl * 6 + c) * a.nl + S.gl] = y[c];
+            for (int c = 0; c < 6; ++c) a.leaf[((size_t)(l0 + nl) * 6 + c) * a.nb + S.row] = y[c];
+          }
           if (S.lane == 0) {
-            lh[nl] = hh;
-            lk[nl] = k;
+            lh[l0 + nl] = hh;
+            lk[l0 + nl] = k;
           }
         }
         ++nl;
@@ -638,6 +646,7 @@ struct StepVals {
   double x2[3], v2[3];  // after the drift (BS for group members)
   double x3[3];         // after the second Sun kick: the closing kick's positions
   int label;            // group label (the smallest member), or -1
+  int l0, nleaf;        // lane `label`: its group's substeps in the pool (nleaf -1: not kept)
 };
 
 // Encounters among the candidate pairs j > i (Hermite test of the drift,
@@ -689,7 +698,7 @@ __device__ __forceinline__ unsigned long long precheck(const HArgs& a, const Sys
     const double rcj = readlane_d(rc, j);
     if (S.act && j > S.lane) {
       const double d0 = xj - x[0], d1 = yj - x[1], d2 = zj - x[2];
-      const double r = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+      const double r = sqrt_nr(d0 * d0 + d1 * d1 + d2 * d2);
       const double rcij = rc > rcj ? rc : rcj;
       if (r < a.pf * rcij) c |= 1ull << j;
     }
@@ -704,9 +713,12 @@ __device__ __forceinline__ double radius(const HArgs& a, const Sys& S, const dou
 }
 
 // One hybrid step of the lane's system: x, v and the candidate bits in and
-// out; R keeps the intermediate values.
+// out; R keeps the intermediate values.  With REC the groups' accepted BS
+// substeps go to the pool from `used` on, while they fit.
+template <bool REC>
 __device__ __forceinline__ void hyb_step(const HArgs& a, const Sys& S, double x[3], double v[3],
-                         unsigned long long& cand, StepVals& R, unsigned& fl) {
+                         unsigned long long& cand, StepVals& R, unsigned& fl, double* lh = nullptr,
+                         int* lk = nullptr, int* used = nullptr) {
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     R.x0[c] = x[c];
@@ -732,6 +744,7 @@ __device__ __forceinline__ void hyb_step(const HArgs& a, const Sys& S, double x[
   R.s = s;
   const int label = groups(a, S, cand, R.x1, R.v1, x, v, rc);
   R.label = label;
+  R.l0 = R.nleaf = 0;
   // BS of each group from the pre-drift state, groups by ascending label
   unsigned long long roots = __builtin_amdgcn_ballot_w64(label == S.lane);
   for (; roots; roots &= roots - 1) {
@@ -739,7 +752,17 @@ __device__ __forceinline__ void hyb_step(const HArgs& a, const Sys& S, double x[
     const bool mem = label == g;
     const unsigned long long M = __builtin_amdgcn_ballot_w64(mem);
     double y[6] = {R.x1[0], R.x1[1], R.x1[2], R.v1[0], R.v1[1], R.v1[2]};
-    if (bs_group<false>(a, S, M, mem, rc, y, nullptr, nullptr, nullptr) < 0) fl |= F_BS;
+    int nl = 0;
+    const int l0 = REC ? *used : 0;
+    if (bs_group<REC>(a, S, M, mem, rc, y, lh, lk, &nl, l0, kHPool - l0) < 0) fl |= F_BS;
+    if (REC) {
+      const bool kept = nl <= kHPool - l0;
+      if (S.lane == g) {
+        R.l0 = l0;
+        R.nleaf = kept ? nl : -1;
+      }
+      if (kept) *used = l0 + nl;
+    }
     if (mem) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
@@ -990,19 +1013,23 @@ __device__ __forceinline__ void gragg_vjp_par(const HArgs& a, const Sys& S, cons
 }
 
 // Adjoint of one group's BS over tau from y1 (the members' pre-drift
-// state): yb holds the adjoint of the BS result in and that of y1 out.
+// state): yb holds the adjoint of the BS result in and that of y1 out.  The
+// group's accepted substeps are nleaf pool entries from l0 on; when the pool
+// had no room for them (nleaf < 0) its BS is rerun to have them behind the pool.
 __device__ __forceinline__ void bs_group_vjp(const HArgs& a, const Sys& S, unsigned long long M, bool mem,
                              double rc, const double y1[6], double yb[6], double& mb, double& rcb,
-                             double* lh, int* lk, unsigned& fl) {
-  double y[6];
+                             double* lh, int* lk, unsigned& fl, int l0, int nleaf) {
+  if (nleaf < 0) {
+    double y[6];
 #pragma unroll
-  for (int c = 0; c < 6; ++c) y[c] = y1[c];
-  int nleaf = 0;
-  const int rcode = bs_group<true>(a, S, M, mem, rc, y, lh, lk, &nleaf);
-  __syncthreads();  // the substeps' lengths and columns (LDS) for every lane
-  if (rcode < 0) {
-    fl |= F_BS;
-    return;
+    for (int c = 0; c < 6; ++c) y[c] = y1[c];
+    l0 = kHPool;
+    const int rcode = bs_group<true>(a, S, M, mem, rc, y, lh, lk, &nleaf, l0, kHLeaf);
+    __syncthreads();  // the substeps' lengths and columns (LDS) for every lane
+    if (rcode < 0) {
+      fl |= F_BS;
+      return;
+    }
   }
   if (nleaf > kHLeaf) {
     fl |= F_ADJ_LEAF;
@@ -1011,11 +1038,13 @@ __device__ __forceinline__ void bs_group_vjp(const HArgs& a, const Sys& S, unsig
   const Par P = par_of(S, M, rc);
   const int qi = __builtin_popcountll(M & ((1ull << S.lane) - 1ull)) & 7;  // body lane's slot
   for (int l = nleaf - 1; l >= 0; --l) {
-    const double hh = lh[l];
-    const int kk = lk[l];
-    double yin[6], acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    const double hh = lh[l0 + l];
+    const int kk = lk[l0 + l];
+    double yin[6] = {1.0, 0.0, 0.0, 0.0, 0.0, 0.0}, acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    if (mem) {
 #pragma unroll
-    for (int c = 0; c < 6; ++c) yin[c] = a.leaf[((size_t)l * 6 + c) * a.nl + S.gl];
+      for (int c = 0; c < 6; ++c) yin[c] = a.leaf[((size_t)(l0 + l) * 6 + c) * a.nb + S.row];
+    }
     if (P.sz <= kHPar) {
       // the columns side by side, then each member's columns added in order
       double y0[6], ob[6], col[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -1142,7 +1171,7 @@ __global__ __launch_bounds__(64) void k_hadj_fwd(HArgs a) {
       c[6 * a.nb + S.row] = __longlong_as_double((long long)cand);
     }
     StepVals R;
-    hyb_step(a, S, x, v, cand, R, fl);
+    hyb_step<false>(a, S, x, v, cand, R, fl);
   }
   if (S.act) {
     a.xm[S.row] = make_double4(x[0], x[1], x[2], S.m);
@@ -1151,9 +1180,50 @@ __global__ __launch_bounds__(64) void k_hadj_fwd(HArgs a) {
   if (fl) atomicOr(a.flags, fl);
 }
 
+// The three-vectors of a step's values, in tape order from 0 on; then s, rc and
+// the group (label, and of lane `label` its pool entries) as one integer.
+__device__ __forceinline__ void tape_put(const HArgs& a, const Sys& S, int t, const StepVals& R) {
+  if (!S.act) return;
+  double* tp = a.tape + (size_t)t * kHTape * a.nb + S.row;
+  const double* q[6] = {R.x0, R.v0, R.x1, R.v1, R.v2, R.x3};
+#pragma unroll
+  for (int k = 0; k < 6; ++k)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) tp[(3 * k + c) * a.nb] = q[k][c];
+  tp[18 * a.nb] = R.s;
+  tp[19 * a.nb] = R.rc;
+  const long long g = (long long)(R.label + 1) | (long long)R.l0 << 8 | (long long)(R.nleaf + 1) << 24;
+  tp[20 * a.nb] = __longlong_as_double(g);
+}
+__device__ __forceinline__ void tape_get(const HArgs& a, const Sys& S, int t, StepVals& R) {
+  double* q[6] = {R.x0, R.v0, R.x1, R.v1, R.v2, R.x3};
+  long long g = 0;
+  if (S.act) {
+    const double* tp = a.tape + (size_t)t * kHTape * a.nb + S.row;
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) q[k][c] = tp[(3 * k + c) * a.nb];
+    R.s = tp[18 * a.nb];
+    R.rc = tp[19 * a.nb];
+    g = __double_as_longlong(tp[20 * a.nb]);
+  } else {
+    // lanes past the system: far away, massless, never read
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) q[k][c] = 0.0;
+    R.x0[0] = R.x1[0] = R.x3[0] = 1.0e3 + S.lane;
+    R.s = R.rc = 0.0;
+  }
+  R.label = (int)(g & 0xFF) - 1;
+  R.l0 = (int)(g >> 8) & 0xFFFF;
+  R.nleaf = (int)(g >> 24) - 1;
+}
+
 __global__ __launch_bounds__(64) void k_hadj_bwd(HArgs a) {
-  __shared__ double lh[kHLeaf];
-  __shared__ int lk[kHLeaf];
+  __shared__ double lh[kHPool + kHLeaf];
+  __shared__ int lk[kHPool + kHLeaf];
   const Sys S = sys_of(a);
   double lx[3] = {0.0, 0.0, 0.0}, lv[3] = {0.0, 0.0, 0.0}, lm = 0.0;
   if (S.act) {
@@ -1178,32 +1248,18 @@ __global__ __launch_bounds__(64) void k_hadj_bwd(HArgs a) {
       }
       cand = (unsigned long long)__double_as_longlong(cp[6 * a.nb + S.row]);
     }
-    // the segment replayed keeping every step's start, then its steps in
-    // reverse, each recomputed from its start (one loop, so that the step's
-    // code appears once)
-    const int ns = t1 - t0;
-    for (int it = 0; it < 2 * ns; ++it) {
-      const bool rev = it >= ns;
-      const int t = rev ? t1 - 1 - (it - ns) : t0 + it;
-      double* tp = a.tape + (size_t)(t - t0) * 7 * a.nl;
-      if (!rev) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          tp[k * a.nl + S.gl] = x[k];
-          tp[(3 + k) * a.nl + S.gl] = v[k];
-        }
-        tp[6 * a.nl + S.gl] = __longlong_as_double((long long)cand);
-      } else {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          x[k] = tp[k * a.nl + S.gl];
-          v[k] = tp[(3 + k) * a.nl + S.gl];
-        }
-        cand = (unsigned long long)__double_as_longlong(tp[6 * a.nl + S.gl]);
-      }
+    // the segment replayed keeping every step's intermediate values and the
+    // groups' accepted substeps, then its steps in reverse
+    int used = 0;
+    for (int t = t0; t < t1; ++t) {
       StepVals R;
-      hyb_step(a, S, x, v, cand, R, fl);
-      if (!rev) continue;
+      hyb_step<true>(a, S, x, v, cand, R, fl, lh, lk, &used);
+      tape_put(a, S, t - t0, R);
+    }
+    __syncthreads();  // lh, lk for every lane
+    for (int t = t1 - 1; t >= t0; --t) {
+      StepVals R;
+      tape_get(a, S, t - t0, R);
       const double rc = R.rc;
       double rcb = 0.0;
       // closing kick: v4 = v2 + h a_B(x3)
@@ -1230,7 +1286,8 @@ __global__ __launch_bounds__(64) void k_hadj_bwd(HArgs a) {
         const unsigned long long M = __builtin_amdgcn_ballot_w64(mem);
         const double y1[6] = {R.x1[0], R.x1[1], R.x1[2], R.v1[0], R.v1[1], R.v1[2]};
         double yb[6] = {xb[0], xb[1], xb[2], vb[0], vb[1], vb[2]};
-        bs_group_vjp(a, S, M, mem, rc, y1, yb, lm, rcb, lh, lk, fl);
+        bs_group_vjp(a, S, M, mem, rc, y1, yb, lm, rcb, lh, lk, fl,
+                     __builtin_amdgcn_readlane(R.l0, g), __builtin_amdgcn_readlane(R.nleaf, g));
         if (mem) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
@@ -1301,9 +1358,9 @@ size_t hadj_ckpt_bytes(int64_t nb, int T, int K) {
   return (size_t)((T + K - 1) / K) * 7 * (size_t)nb * sizeof(double);
 }
 
-size_t hadj_work_bytes(int nsys, int K) {
-  const size_t nl = (size_t)nsys * 64;
-  return nl * sizeof(double) * (7 * (size_t)K + 6 * kHLeaf + 3 * kHPos);
+size_t hadj_work_bytes(int nsys, int64_t nb, int K) {
+  return sizeof(double) * ((size_t)nb * (kHTape * (size_t)K + 6 * (kHPool + kHLeaf)) +
+                           (size_t)nsys * 64 * 3 * kHPos);
 }
 
 hipError_t hadj_forward(const BatchWs& b, const StepConsts& c, int T, int K, double* ckpt,
@@ -1319,10 +1376,10 @@ hipError_t hadj_backward(const BatchWs& b, const StepConsts& c, int T, int K, do
                          double* gv0, double* gm, hipStream_t s) {
   HArgs a = hargs(b, c, T, K);
   a.ckpt = ckpt;
-  const size_t nl = (size_t)b.nsys * 64;
+  const size_t nb = (size_t)b.nb;
   a.tape = work;
-  a.leaf = a.tape + nl * 7 * (size_t)K;
-  a.zpos = a.leaf + nl * 6 * (size_t)kHLeaf;
+  a.leaf = a.tape + nb * kHTape * (size_t)K;
+  a.zpos = a.leaf + nb * 6 * (size_t)(kHPool + kHLeaf);
   a.gxT = gxT;
   a.gvT = gvT;
   a.gx0 = gx0;

@@ -249,3 +249,28 @@ def test_hybrid_small_systems():
             err = _rel(g, o)
             _say("system of", sizes[s], "encounters", st["enc_total"], "d/d" + what, err)
             assert err <= 1e-9, (s, what, err)
+
+
+# one segment per step never fills the store of BS substeps that the replay
+# keeps (64); one segment for all steps does, and integrates the groups that
+# found no room again: the same substeps, so the same gradient
+@pytest.mark.parametrize("ckpt", [1, 17, 96])
+def test_hybrid_gradient_independent_of_segments(ckpt):
+    print("hybrid segments ckpt", ckpt, flush=True)
+    nsys, npl, T = 6, 8, 96
+    m, x, u = W.encounter_systems(nsys, npl, seed_index=51)
+    off = np.arange(0, nsys * npl + 1, npl, dtype=np.int32)
+    args = (off, np.ones(nsys), m.reshape(-1), x.reshape(-1, 3), u.reshape(-1, 3))
+    run = G.BatchedSimulation(*args, G.default_params())
+    run.step(T)
+    assert run.stats()["bs_substeps"] > 64 * nsys
+    rng = np.random.default_rng(8)
+    gx, gv = rng.standard_normal((2, nsys * npl, 3))
+    out = []
+    for k in (ckpt, 2):
+        sim = G.BatchedSimulation(*args, G.default_params())
+        sim.adj_forward(T, k)
+        out.append([t.cpu().numpy() for t in sim.adj_backward(gx, gv)])
+        sim.check()
+    for a, b in zip(*out):
+        assert np.abs(a - b).max() <= 1e-12 * np.abs(b).max()
