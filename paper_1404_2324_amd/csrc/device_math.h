@@ -209,15 +209,15 @@ __device__ __forceinline__ void stumpff(double z, double& c0, double& c1,
 // when its corrections are small against t (short steps); otherwise s = t.
 // The Stumpff values of the last residual evaluation are reused for f and g
 // when the iteration stopped there; 1/r0 and 1/r are formed once and
-// multiplied in.  Returns the iteration count, or a
+// multiplied in; roots and quotients by the short forms above (the same bits).  Returns the iteration count, or a
 // negative count when max_iter was reached without convergence.
 // s_out (optional) receives the converged universal anomaly s.
 __device__ __forceinline__ int kepler_drift(double mu, double dt, double& x,
                                             double& y, double& z, double& vx,
                                             double& vy, double& vz,
                                             int max_iter, double* s_out = nullptr) {
-  const double r0 = sqrt(x * x + y * y + z * z);
-  const double ir0 = 1.0 / r0;
+  const double r0 = sqrt_nr(x * x + y * y + z * z);
+  const double ir0 = rcp_nr(r0);
   const double eta0 = x * vx + y * vy + z * vz;
   const double beta = 2.0 * mu * ir0 - (vx * vx + vy * vy + vz * vz);
   const double zeta0 = mu - beta * r0;
@@ -242,8 +242,8 @@ __device__ __forceinline__ int kepler_drift(double mu, double dt, double& x,
     const double Fp = r0 + eta0 * G1 + zeta0 * G2;
     const double Fpp = eta0 * c0 + zeta0 * G1;
     const double disc = 16.0 * Fp * Fp - 20.0 * F * Fpp;
-    const double sq = sqrt(fabs(disc));
-    const double ds = -5.0 * F / (Fp + copysign(sq, Fp));
+    const double sq = sqrt_nr(fmax(fabs(disc), 1e-280));  // (a zero would give NaN)
+    const double ds = div_nr(-5.0 * F, Fp + copysign(sq, Fp));
     s += ds;
     if (fabs(ds) <= 0x1p-50 * fabs(s)) {
       ok = true;
@@ -254,7 +254,7 @@ __device__ __forceinline__ int kepler_drift(double mu, double dt, double& x,
   if (!fresh) stumpff(beta * s * s, c0, c1, c2, c3);
   const double G1 = s * c1, G2 = s * s * c2, G3 = s * s * s * c3;
   const double r = r0 + eta0 * G1 + zeta0 * G2;
-  const double ir = 1.0 / r;
+  const double ir = rcp_nr(r);
   const double f = 1.0 - mu * G2 * ir0;
   const double g = dt - mu * G3;
   const double fd = -mu * G1 * ir0 * ir;
@@ -302,9 +302,10 @@ __device__ __forceinline__ double hermite_dmin2(double dt, double dx0,
   if (a != 0.0) {
     const double disc = b * b - 4.0 * a * c;
     if (disc >= 0.0) {
-      const double q = -0.5 * (b + copysign(sqrt(disc), b));
-      t1 = q / a;
-      if (q != 0.0) t2 = c / q;
+      const double sq = disc > 0.0 ? sqrt_nr(disc) : 0.0;
+      const double q = -0.5 * (b + copysign(sq, b));
+      t1 = div_nr(q, a);
+      if (q != 0.0) t2 = div_nr(c, q);
     }
   } else if (b != 0.0) {
     t1 = -c / b;

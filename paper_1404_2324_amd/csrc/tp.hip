@@ -155,12 +155,31 @@ __device__ __forceinline__ void tp_finish(const TpArgs& a, const double4* __rest
   a.mask[k] = msk;
 }
 
-// The planets' states of the step, as kernel arguments of their own: noalias
-// parameters' wave-uniform loads become scalar loads.
+// The planets' states of the step that the kicks take, as kernel arguments of
+// their own: noalias parameters' wave-uniform loads become scalar loads.
 struct TpPlanets {
-  const double4 *px0, *pfin, *ppre, *vpre, *ppost, *vpost;
+  const double4 *px0, *pfin;
   const double* rc;
 };
+// What the Hermite test takes of a planet: its state before and after the
+// drift and its radius, in LDS, since each lane tests its own candidates.
+typedef double TpDrift[13][kTpMaxPlanets];
+__device__ __forceinline__ void tp_load_drift(const TpArgs& a, const double4* ppre,
+                                              const double4* vpre, const double4* ppost,
+                                              const double4* vpost, const double* rc,
+                                              TpDrift& sp) {
+  const int j = threadIdx.x;
+  if (j < a.nm) {
+    const double4 q[4] = {ppre[j], vpre[j], ppost[j], vpost[j]};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      sp[3 * c][j] = q[c].x;
+      sp[3 * c + 1][j] = q[c].y;
+      sp[3 * c + 2][j] = q[c].z;
+    }
+    sp[12][j] = rc[j];
+  }
+}
 
 // What a particle with an encounter leaves for its BS.
 struct TpListed {
@@ -172,7 +191,8 @@ struct TpListed {
 // One particle's step up to its BS.
 __device__ __forceinline__ TpListed tp_particle(const TpArgs& a, const TpPlanets& pl, int64_t k,
                                                 double P1x, double P1y, double P1z, double P2x,
-                                                double P2y, double P2z, unsigned* kh) {
+                                                double P2y, double P2z, const TpDrift& sp,
+                                                unsigned* kh) {
   TpListed L;
   double x = a.x[k];
   if (isnan(x)) return L;
@@ -198,15 +218,17 @@ __device__ __forceinline__ TpListed tp_particle(const TpArgs& a, const TpPlanets
   L.it = kepler_drift(a.mu, a.dt, x, y, z, vx, vy, vz, a.max_iter);
   if (L.it < 0) atomicOr(&a.st->flags, F_KEPLER);
   atomicAdd(&kh[min(abs(L.it), kKepBins - 1)], 1u);
-  if (!a.enc_free && cmask) {
-    for (int j = 0; j < a.nm; ++j) {
-      if (!(cmask & (1u << j))) continue;
-      const double4 p0 = pl.ppre[j], q0 = pl.vpre[j], p1 = pl.ppost[j], q1 = pl.vpost[j];
-      const double d2 = hermite_dmin2(a.dt, p0.x - L.x, p0.y - L.y, p0.z - L.z,
-                                      q0.x - L.vx, q0.y - L.vy, q0.z - L.vz,
-                                      p1.x - x, p1.y - y, p1.z - z,
-                                      q1.x - vx, q1.y - vy, q1.z - vz);
-      const double rcij = fmax(rct, pl.rc[j]);
+  if (!a.enc_free) {
+    // the lane's own candidates, so a pass serves one of every lane: a few
+    // passes a wave instead of one per planet (some lane of a wave has nearly
+    // every planet as a candidate)
+    for (unsigned mc = cmask; mc; mc &= mc - 1u) {
+      const int j = __ffs(mc) - 1;
+      const double d2 = hermite_dmin2(a.dt, sp[0][j] - L.x, sp[1][j] - L.y, sp[2][j] - L.z,
+                                      sp[3][j] - L.vx, sp[4][j] - L.vy, sp[5][j] - L.vz,
+                                      sp[6][j] - x, sp[7][j] - y, sp[8][j] - z,
+                                      sp[9][j] - vx, sp[10][j] - vy, sp[11][j] - vz);
+      const double rcij = fmax(rct, sp[12][j]);
       if (d2 < rcij * rcij) {
         L.emask |= 1u << j;
         a.enc_d2[(size_t)j * a.ntp + k] = d2;
@@ -255,7 +277,9 @@ __global__ __launch_bounds__(256) void k_tp_main(TpArgs a, TpSlot sl,
     return;
   }
   __shared__ unsigned kh[kKepBins];  // this block's drifts by iteration count
+  __shared__ TpDrift sp;
   if (threadIdx.x < kKepBins) kh[threadIdx.x] = 0u;
+  tp_load_drift(a, ppre, vpre, ppost, vpost, prc, sp);
   __syncthreads();
   const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int lane = threadIdx.x & 63;
@@ -271,8 +295,8 @@ __global__ __launch_bounds__(256) void k_tp_main(TpArgs a, TpSlot sl,
     if (a.busy[k]) {
       a.busy[k] = 0;  // still in the last step's refinement: the late pass takes it
     } else {
-      const TpPlanets pl = {px0, pfin, ppre, vpre, ppost, vpost, prc};
-      L = tp_particle(a, pl, k, P1x, P1y, P1z, P2x, P2y, P2z, kh);
+      const TpPlanets pl = {px0, pfin, prc};
+      L = tp_particle(a, pl, k, P1x, P1y, P1z, P2x, P2y, P2z, sp, kh);
     }
   }
   const bool listed = L.emask != 0u;
@@ -325,6 +349,9 @@ __global__ __launch_bounds__(64) void k_tp_late(TpArgs a, const double4* __restr
                                                 const double4* __restrict__ vpost,
                                                 const double* __restrict__ prc) {
   __shared__ unsigned kh[kKepBins];
+  __shared__ TpDrift sp;
+  tp_load_drift(a, ppre, vpre, ppost, vpost, prc, sp);
+  __syncthreads();
   const int nq = *a.prq_cnt;
   double P1x = 0.0, P1y = 0.0, P1z = 0.0;
   for (int b = 0; b < a.nblk; ++b) {
@@ -333,13 +360,13 @@ __global__ __launch_bounds__(64) void k_tp_late(TpArgs a, const double4* __restr
     P1z += a.partP[4 * b + 2];
   }
   const double P2x = a.P2[0], P2y = a.P2[1], P2z = a.P2[2];
-  const TpPlanets pl = {px0, pfin, ppre, vpre, ppost, vpost, prc};
+  const TpPlanets pl = {px0, pfin, prc};
   // a few particles per wave: the queue is short, and a wave takes every
   // branch that one of its particles needs
   if (threadIdx.x >= kTpLateLanes) return;
   for (int q = blockIdx.x * kTpLateLanes + threadIdx.x; q < nq; q += gridDim.x * kTpLateLanes) {
     const int64_t k = a.pidx[a.prq[q]];
-    const TpListed L = tp_particle(a, pl, k, P1x, P1y, P1z, P2x, P2y, P2z, kh);
+    const TpListed L = tp_particle(a, pl, k, P1x, P1y, P1z, P2x, P2y, P2z, sp, kh);
     if (L.it == 0) continue;  // removed in that refinement
     const int64_t b = k >> 8;
     atomicMax(&a.blk_kit[b], abs(L.it));
