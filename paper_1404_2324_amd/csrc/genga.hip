@@ -151,7 +151,8 @@ static hipError_t record_tp_steps(genga_ctx* ctx, int nsteps, std::vector<hipEve
   const bool side = nsteps > 1 && !ctx->c.encounter_free && ctx->t.ntp >= kTpOverlap;
   for (int k = 0; k < nsteps; ++k) {
     const bool defer = side && k + 1 < nsteps;
-    if (!ok(massive_step(ctx->w, ctx->sub[0], s, nullptr, ctx->t.slot[k].cnt)) ||
+    int* cnt = ctx->t.slot[k].cnt;
+    if (!ok(massive_step(ctx->w, ctx->sub[0], s, nullptr, cnt)) ||
         !ok(tp_main(ctx->w, ctx->t, ctx->c, k, defer, s)))
       return e;
     if (side && k > 0 &&
@@ -173,9 +174,12 @@ static int capture(genga_ctx* ctx, int nsteps, hipGraphExec_t* out) {
   if (ctx->mode == GENGA_TEST) {
     e = record_tp_steps(ctx, nsteps, ev);
   } else {
-    for (int k = 0; k < nsteps && e == hipSuccess; ++k)
-      for (size_t q = 0; q < ctx->sub.size() && e == hipSuccess; ++q)
-        e = massive_step(ctx->w, ctx->sub[q], ctx->cap);
+    if (ctx->sub.size() == 1 && massive_small(ctx->w, ctx->sub[0]))
+      e = massive_small_steps(ctx->w, ctx->sub[0], nsteps, ctx->cap);
+    else
+      for (int k = 0; k < nsteps && e == hipSuccess; ++k)
+        for (size_t q = 0; q < ctx->sub.size() && e == hipSuccess; ++q)
+          e = massive_step(ctx->w, ctx->sub[q], ctx->cap);
   }
   hipError_t e2 = hipStreamEndCapture(ctx->cap, &g);
   for (hipEvent_t q : ev) (void)hipEventDestroy(q);

@@ -226,6 +226,10 @@ constexpr int kSlotPairs = 3;  // the pair kernel's slot
 // tpcnt: test-particle list counts (three) that the step's first kernel clears.
 hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
                         const hipEvent_t* kev = nullptr, int* tpcnt = nullptr);
+// nsteps steps of a small system in one launch, when massive_small says that it
+// takes them; the same results as massive_step, bit for bit.
+bool massive_small(const MassiveWs& w, const StepConsts& c);
+hipError_t massive_small_steps(const MassiveWs& w, const StepConsts& c, int nsteps, hipStream_t s);
 hipError_t massive_energy(const MassiveWs& w, const StepConsts& c, double* dE,
                           double* dL, hipStream_t s);
 // H_B acceleration of positions x (w = mass; x = xs for a context's state).

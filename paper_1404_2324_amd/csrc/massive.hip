@@ -1715,6 +1715,351 @@ __global__ __launch_bounds__(64 * kBsWaves, LB) void k_group_bs(EncArgs e, BsArg
   bs_groups(a, ng, L.g.gof, L.gm, L.b);
 }
 
+// ---- whole steps of a small system in one workgroup --------------------------
+// Up to kSmallN bodies (a planetary system) in main mode, the plain step
+// without bodies leaving: every phase of the step in one
+// launch, nsteps steps of them, where five launches of one or few workgroups
+// each pay their start, their loads and their drain.  Bound by the chain of
+// one step (Kepler drift, pair terms, radii) on one wave: 16 bodies without
+// encounters 17.0 -> 6.8 us a step in calls of 16 steps, 22.7 -> 19.6 in calls
+// of one.
+// Lane i of wave 0 holds body i through the steps; the other waves share
+// the pair sums and the BS.  Every sum is formed in the order of the separate
+// kernels (candidates ascending; pair terms two by two as their 16 waves take
+// them), so both give the same bits.  The candidate rows live as bit masks and
+// go back to the table at the end.
+constexpr int kSmallN = 16;
+constexpr int kSmallW = 4;  // waves
+static_assert(kSmallW == kBsWaves, "the workgroup integrates the groups");
+
+struct SmallArgs {
+  OpenArgs o;
+  EncArgs e;
+  BsArgs b;
+  PairArgs p;
+  int nsteps;
+};
+
+struct SmallLds {
+  GroupBsLds<kSmallN, kSmallN * kSmallN / 2> g;
+  double4 x[kSmallN];               // positions and masses
+  double rc[kSmallN];               // radii
+  double thr[kSmallN];
+  double hs[12][kSmallN];           // before and after the drift: x, v, x, v
+  double red[6][kSmallN / 2][kSmallN];  // pair sums, two partners each
+  unsigned near[kSmallN / 2][kSmallN];  // candidates among the two partners
+  unsigned kh[kKepBins];
+  int ne;
+};
+
+__global__ __launch_bounds__(64 * kSmallW) void k_small_steps(SmallArgs A) {
+  __shared__ SmallLds L;
+  const OpenArgs& o = A.o;
+  const EncArgs& e = A.e;
+  const PairArgs& a = A.p;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  DevStat* st = o.st;
+  if (st->flags & F_NMIN) {  // the run stopped below nmin bodies
+    if (tid == 0) st->stopped = 1;
+    return;
+  }
+  // rows past the live count are massless padding: exact zeros in every sum
+  const int n = __builtin_amdgcn_readfirstlane(min(o.n, st->nlive)), i = lane;
+  const bool w0 = wave == 0, act = w0 && i < n;
+  double4 p = make_double4(0.0, 0.0, 0.0, 0.0), v = p, af = p;
+  double rcn = 0.0, rci = 0.0;
+  unsigned cand = 0u;
+  bool full = false;
+  double P2x = 0.0, P2y = 0.0, P2z = 0.0;
+  int itmax = 0;
+  if (tid < kKepBins) L.kh[tid] = 0u;
+  if (w0) {
+    full = (st->ctl & C_FULLKICK) != 0;
+    P2x = st->P2[0];
+    P2y = st->P2[1];
+    P2z = st->P2[2];
+  }
+  if (act) {
+    p = o.xs[i];
+    v = o.vv[i];
+    af = o.afar[i];
+    rcn = o.rc_next[i];
+    const int cnt = min(o.ccnt[i], o.cpb);
+    for (int u = 0; u < cnt; ++u) cand |= 1u << o.ctab[(size_t)i * o.cpb + u];
+  }
+  __syncthreads();
+  for (int step = 0; step < A.nsteps; ++step) {
+    const bool last = step + 1 == A.nsteps;
+    double4 pre = p, vpre = v;
+    double Qx = 0.0, Qy = 0.0, Qz = 0.0;
+    if (w0) {
+      // opening kick, Sun kick, drift (k_open_drift)
+      if (act) {
+        L.x[i] = p;
+        L.rc[i] = rcn;
+      }
+      wsync();
+      double m = 0.0, kx = 0.0, ky = 0.0, kz = 0.0, dx = 0.0, dy = 0.0, dz = 0.0;
+      double tloc = kTiny;
+      int it = 0;
+      const double Ps = o.h / o.m0;
+      const double sx = Ps * P2x, sy = Ps * P2y, sz = Ps * P2z;
+      if (act) {
+        rci = rcn;
+        double ax = 0.0, ay = 0.0, az = 0.0;
+        if (full) {
+          for (int j = 0; j < n; ++j)
+            if (j != i) pair_hb(p.x, p.y, p.z, rci, L.x[j], L.rc[j], o.encounter_free, ax, ay, az);
+          ax *= o.G;
+          ay *= o.G;
+          az *= o.G;
+        } else {
+          double cx = 0.0, cy = 0.0, cz = 0.0;
+          for (unsigned c = cand; c; c &= c - 1u) {
+            const int j = __ffs(c) - 1;
+            pair_hb(p.x, p.y, p.z, rci, L.x[j], L.rc[j], o.encounter_free, cx, cy, cz);
+          }
+          ax = af.x + o.G * cx;
+          ay = af.y + o.G * cy;
+          az = af.z + o.G * cz;
+        }
+        v.x += o.h * ax;
+        v.y += o.h * ay;
+        v.z += o.h * az;
+        tloc = o.encounter_free ? kTiny : fmax(o.pf2 * rci * rci, kTiny);
+        m = p.w;
+        kx = v.x;
+        ky = v.y;
+        kz = v.z;
+        double x = p.x + sx, y = p.y + sy, z = p.z + sz;
+        pre = make_double4(x, y, z, 0.0);
+        vpre = make_double4(v.x, v.y, v.z, 0.0);
+        dx = v.x;
+        dy = v.y;
+        dz = v.z;
+        it = kepler_drift(o.mu, o.dt, x, y, z, dx, dy, dz, o.max_iter);
+        if (it < 0) atomicOr(&st->flags, F_KEPLER);
+        atomicAdd(&L.kh[min(abs(it), kKepBins - 1)], 1u);
+        p.x = x;
+        p.y = y;
+        p.z = z;
+        v = make_double4(dx, dy, dz, 0.0);
+      }
+      itmax = max(itmax, wave_max_i(abs(it)));
+      const double Px = wave_sum(m * kx), Py = wave_sum(m * ky), Pz = wave_sum(m * kz);
+      Qx = wave_sum(m * dx);
+      Qy = wave_sum(m * dy);
+      Qz = wave_sum(m * dz);
+      if (act) {
+        L.x[i] = p;
+        L.thr[i] = tloc;
+        if (!o.encounter_free) {
+          const double q[12] = {pre.x, pre.y, pre.z, vpre.x, vpre.y, vpre.z,
+                                p.x,   p.y,   p.z,   v.x,    v.y,    v.z};
+#pragma unroll
+          for (int c = 0; c < 12; ++c) L.hs[c][i] = q[c];
+        }
+      }
+      wsync();
+      // encounter search (k_encounter): the lane's candidates j > i; pairs in
+      // the list in body order
+      unsigned enc = 0u;
+      if (act && !o.encounter_free) {
+        for (unsigned c = cand & ~((2u << i) - 1u); c; c &= c - 1u) {
+          const int j = __ffs(c) - 1;
+          const double d2 = hermite_dmin2(
+              e.dt, L.hs[0][j] - pre.x, L.hs[1][j] - pre.y, L.hs[2][j] - pre.z,
+              L.hs[3][j] - vpre.x, L.hs[4][j] - vpre.y, L.hs[5][j] - vpre.z, L.hs[6][j] - p.x,
+              L.hs[7][j] - p.y, L.hs[8][j] - p.z, L.hs[9][j] - v.x, L.hs[10][j] - v.y,
+              L.hs[11][j] - v.z);
+          const double rcij = fmax(rci, L.rc[j]);
+          if (d2 < rcij * rcij) enc |= 1u << j;
+        }
+      }
+      int at = __popc(enc), ne = at;
+      for (int s = 1; s < 64; s <<= 1) {
+        const int t = __shfl_up(at, s, 64);
+        if (lane >= s) at += t;
+      }
+      ne = __shfl(at, 63, 64);
+      at -= __popc(enc);
+      for (unsigned c = enc; c; c &= c - 1u, ++at) {
+        if (at >= e.enc_cap) break;
+        const int j = __ffs(c) - 1;
+        const double rcij = fmax(rci, L.rc[j]);
+        e.encij[at] = make_int2(i, j);
+        e.encd2[at] = hermite_dmin2(
+            e.dt, L.hs[0][j] - pre.x, L.hs[1][j] - pre.y, L.hs[2][j] - pre.z, L.hs[3][j] - vpre.x,
+            L.hs[4][j] - vpre.y, L.hs[5][j] - vpre.z, L.hs[6][j] - p.x, L.hs[7][j] - p.y,
+            L.hs[8][j] - p.z, L.hs[9][j] - v.x, L.hs[10][j] - v.y, L.hs[11][j] - v.z);
+        e.encrc2[at] = rcij * rcij;
+      }
+      int rows = act ? min(__popc(cand), o.cpb) : 0;
+      for (int s = 32; s > 0; s >>= 1) rows += __shfl_xor(rows, s, 64);
+      if (lane == 0) {
+        L.ne = ne;
+        if (full) st->fullkicks += 1ull;
+        st->nenc = ne;
+        st->ncand = rows / 2;
+        if (ne == 0) {
+          st->ngroups = 0;
+          st->maxg = 0;
+        }
+        st->nstep += 1ull;
+        if (last) {
+          o.partP[0] = Px;
+          o.partP[1] = Py;
+          o.partP[2] = Pz;
+          o.partP2[0] = Qx;
+          o.partP2[1] = Qy;
+          o.partP2[2] = Qz;
+        }
+      }
+      // what the groups' BS reads, and the callers after the last step
+      if (act && (ne > 0 || last)) {
+        o.xm[i] = p;
+        o.vv[i] = v;
+        o.xpre[i] = pre;
+        o.vpre[i] = vpre;
+        o.rc_cur[i] = rci;
+      }
+    }
+    __syncthreads();
+    const int ne = __builtin_amdgcn_readfirstlane(L.ne);
+    int ng = 0;
+    if (ne > 0) {
+      // (the row counts it sums for st->ncand and clears are the table's, not
+      // these steps': both are set from the masks)
+      ng = group_phase<64 * kSmallW>(e, ne, L.g.g, L.g.gm, true);
+      bs_groups(A.b, ng, L.g.g.gof, L.g.gm, L.g.b);
+      if (w0) {
+        if (act) {
+          p = o.xm[i];
+          v = o.vv[i];
+          L.x[i] = p;
+        }
+        int rows = act ? min(__popc(cand), o.cpb) : 0;
+        for (int s = 32; s > 0; s >>= 1) rows += __shfl_xor(rows, s, 64);
+        if (lane == 0) st->ncand = rows / 2;
+      }
+      __syncthreads();
+    }
+    // closing kick (k_pair_part): half-wave h takes partners (2 t, 2 t + 1) of
+    // t = 2 wave + h; the pair kernel's other waves hold padding, whose sums are 0
+    {
+      const int b = lane & (kSmallN - 1);  // (two lanes of a half-wave form the same sum)
+      const double4 pi = b < n ? L.x[b] : make_double4(0.0, 0.0, 0.0, 0.0);
+      const double ti = b < n ? L.thr[b] : kTiny, rb = b < n ? L.rc[b] : 0.0;
+      {
+        const int t = 2 * wave + (lane >> 5);
+        double f[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        unsigned near = 0u;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int j = 2 * t + q;
+          if (j >= n || b >= n) continue;  // massless padding: exact zeros
+          const double4 pj = L.x[j];
+          const double dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
+          const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
+          if (r2 < ti || r2 < L.thr[j]) {
+            if (j != b) {
+              const double ir = rsqrt_nr(r2);
+              const double ir2 = ir * ir;
+              double K = 1.0, dK = 0.0;
+              if (!a.encounter_free) changeover(r2 * ir, fmax(rb, L.rc[j]), K, dK);
+              const double sn = pj.w * (K * ir2 * ir - dK * ir2);
+              f[3] += sn * dx;
+              f[4] += sn * dy;
+              f[5] += sn * dz;
+              if (!a.encounter_free) near |= 1u << q;
+            }
+          } else {
+            const double s = m_rinv3(pj.w, r2);
+            f[0] = fma(s, dx, f[0]);
+            f[1] = fma(s, dy, f[1]);
+            f[2] = fma(s, dz, f[2]);
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < 6; ++c) L.red[c][t][b] = f[c];
+        L.near[t][b] = near;
+      }
+    }
+    __syncthreads();
+    if (w0) {
+      // the sums, second Sun kick, velocity, next radii (k_pair_finish)
+      double Px = lane == 0 ? Qx : 0.0, Py = lane == 0 ? Qy : 0.0, Pz = lane == 0 ? Qz : 0.0;
+      if (lane < ng) {
+        Px += a.dP[4 * lane + 0];
+        Py += a.dP[4 * lane + 1];
+        Pz += a.dP[4 * lane + 2];
+      }
+      Px = wave_sum(Px);
+      Py = wave_sum(Py);
+      Pz = wave_sum(Pz);
+      P2x = Px;
+      P2y = Py;
+      P2z = Pz;
+      bool grew = false;
+      if (act) {
+        double S[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        cand = 0u;
+#pragma unroll
+        for (int t = 0; t < kSmallN / 2; ++t) {
+#pragma unroll
+          for (int c = 0; c < 6; ++c) S[c] += L.red[c][t][i];
+          cand |= L.near[t][i] << (2 * t);
+        }
+        if (__popc(cand) > o.cpb) atomicOr(&st->flags, F_CAND_OVF);
+        const double G = a.G;
+        af = make_double4(G * S[0], G * S[1], G * S[2], 0.0);
+        p.x += a.h * Px / a.m0;
+        p.y += a.h * Py / a.m0;
+        p.z += a.h * Pz / a.m0;
+        v.x += a.h * (G * (S[0] + S[3]));
+        v.y += a.h * (G * (S[1] + S[4]));
+        v.z += a.h * (G * (S[2] + S[5]));
+        rcn = rcrit(p.x, p.y, p.z, v.x, v.y, v.z, p.w, a.mu, a.m0, a.n1, a.n2, a.absdt);
+        grew = !a.encounter_free && rcn > a.pf * rci;
+      }
+      full = __ballot(grew) != 0ull;
+    }
+  }
+  if (!w0) return;
+  // the state between launches
+  double tl = kTiny;
+  if (act) {
+    a.xs[i] = p;
+    a.vv[i] = v;
+    a.afar[i] = af;
+    a.rc_next[i] = rcn;
+    tl = L.thr[i];
+    o.thr[i] = tl;
+    if (!o.encounter_free) {
+      int u = 0;
+      for (unsigned c = cand; c; c &= c - 1u, ++u) {
+        if (u >= o.cpb) continue;
+        const int j = __ffs(c) - 1;
+        const double4 pi = L.x[i], pj = L.x[j];
+        const double dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
+        a.ctab[(size_t)i * o.cpb + u] = j;
+        a.cr2[(size_t)i * o.cpb + u] = fma(dx, dx, fma(dy, dy, dz * dz));
+      }
+      a.ccnt[i] = u;
+    }
+  }
+  chunk_tmax(tl, 0, o.tmax64);
+  if (lane < kKepBins) o.khist[lane] += L.kh[lane];
+  if (lane == 0) {
+    if (itmax > st->kep_itmax) atomicMax(&st->kep_itmax, itmax);
+    st->P2[0] = P2x;
+    st->P2[1] = P2y;
+    st->P2[2] = P2z;
+    st->ctl = full ? C_FULLKICK : 0u;
+  }
+}
+
 // ---- bodies leaving the system (Sec. 3.2.7, 3.2.8, 3.4.6) ------------------
 struct CompactArgs {
   double4* __restrict__ xs;
@@ -2400,19 +2745,9 @@ hipError_t massive_accel(const MassiveWs& w, const StepConsts& c, const double4*
   return hipGetLastError();
 }
 
-// Launch of kernel slot `slot` of the step; with kev, through hipExtLaunch so
-// that the slot's two events take the dispatch's own start and end.
-#define STEP_LAUNCH(slot, K, g, b, ...)                                             \
-  do {                                                                              \
-    if (kev)                                                                        \
-      hipExtLaunchKernelGGL(K, g, b, 0, s, kev[2 * (slot)], kev[2 * (slot) + 1], 0, \
-                            __VA_ARGS__);                                           \
-    else                                                                            \
-      hipLaunchKernelGGL(K, g, b, 0, s, __VA_ARGS__);                               \
-  } while (0)
+namespace {
 
-hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
-                        const hipEvent_t* kev, int* tpcnt) {
+OpenArgs open_args(const MassiveWs& w, const StepConsts& c, int* tpcnt) {
   OpenArgs o;
   o.xs = w.xs;
   o.xm = w.xm;
@@ -2444,53 +2779,103 @@ hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
   o.m0 = c.m0;
   o.mu = c.mu;
   o.dt = c.dt;
+  return o;
+}
+
+EncArgs enc_args(const MassiveWs& w, const StepConsts& c) {
+  EncArgs e;
+  e.xm = w.xm;
+  e.vv = w.vv;
+  e.xpre = w.xpre;
+  e.vpre = w.vpre;
+  e.rc = w.rc_cur;
+  e.ccnt = w.ccnt;
+  e.ctab = w.ctab;
+  e.encij = w.encij;
+  e.encd2 = w.encd2;
+  e.encrc2 = w.encrc2;
+  e.goff = w.goff;
+  e.gmem = w.gmem;
+  e.st = w.st;
+  e.n = w.n;
+  e.cpb = w.cpb;
+  e.enc_cap = w.enc_cap;
+  e.dt = c.dt;
+  return e;
+}
+
+BsArgs bs_args(const MassiveWs& w, const StepConsts& c) {
+  BsArgs b;
+  b.xm = w.xm;
+  b.vv = w.vv;
+  b.dP = w.dP;
+  b.xpre = w.xpre;
+  b.vpre = w.vpre;
+  b.rc = w.rc_cur;
+  b.goff = w.goff;
+  b.gmem = w.gmem;
+  b.big = w.bsbig;
+  b.bpos = w.bspos;
+  b.bmem = w.bsmem;
+  b.rc_w = w.rc_cur;
+  b.rad = w.rad;
+  b.sp = w.sp;
+  b.ids = w.ids;
+  b.dead = w.dead;
+  b.ev = w.ev;
+  b.st = w.st;
+  b.G = c.G;
+  b.Gm0 = c.mu;
+  b.dt = c.dt;
+  b.tol = c.bs_tol;
+  b.max_depth = c.bs_max_depth;
+  b.coll = c.coll;
+  b.ev_cap = w.ev_cap;
+  return b;
+}
+
+}  // namespace
+
+// Whether the small-system kernel takes these steps: no composed step (its
+// search goes over all pairs), no bodies leaving, at most kSmallN bodies.  The
+// line lies there because its one workgroup integrates a step's groups one
+// after another, the separate kernels each in a workgroup of its own.  us a
+// step in calls of 16, separate kernels against this one: 16 bodies without
+// encounters 17.0 / 6.8, with two groups of two 31.8 / 24.7; 8 bodies in one
+// group 35.8 / 30.2.  It loses only where 9 to 16 bodies form one group, which
+// one wave integrates on either path: 16 bodies 179 / 188, of which 4 the BS
+// alone (17 bodies, not taken, 189 / 193 against the same older BS).  32 bodies
+// without encounters 17.7 / 7.6, but with 6 groups 47.3 / 63.6.
+bool massive_small(const MassiveWs& w, const StepConsts& c) {
+  return w.n <= kSmallN && !c.all_pairs && !c.phys && !c.coll;
+}
+
+hipError_t massive_small_steps(const MassiveWs& w, const StepConsts& c, int nsteps, hipStream_t s) {
+  const SmallArgs a = {open_args(w, c, nullptr), enc_args(w, c), bs_args(w, c), pair_args(w, c),
+                       nsteps};
+  hipLaunchKernelGGL(k_small_steps, dim3(1), dim3(64 * kSmallW), 0, s, a);
+  return hipGetLastError();
+}
+
+// Launch of kernel slot `slot` of the step; with kev, through hipExtLaunch so
+// that the slot's two events take the dispatch's own start and end.
+#define STEP_LAUNCH(slot, K, g, b, ...)                                             \
+  do {                                                                              \
+    if (kev)                                                                        \
+      hipExtLaunchKernelGGL(K, g, b, 0, s, kev[2 * (slot)], kev[2 * (slot) + 1], 0, \
+                            __VA_ARGS__);                                           \
+    else                                                                            \
+      hipLaunchKernelGGL(K, g, b, 0, s, __VA_ARGS__);                               \
+  } while (0)
+
+hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
+                        const hipEvent_t* kev, int* tpcnt) {
+  const OpenArgs o = open_args(w, c, tpcnt);
   STEP_LAUNCH(0, k_open_drift, dim3(w.nblk), dim3(kOpenBlock), o);
 
   if (!c.encounter_free) {
-    EncArgs e;
-    e.xm = w.xm;
-    e.vv = w.vv;
-    e.xpre = w.xpre;
-    e.vpre = w.vpre;
-    e.rc = w.rc_cur;
-    e.ccnt = w.ccnt;
-    e.ctab = w.ctab;
-    e.encij = w.encij;
-    e.encd2 = w.encd2;
-    e.encrc2 = w.encrc2;
-    e.goff = w.goff;
-    e.gmem = w.gmem;
-    e.st = w.st;
-    e.n = w.n;
-    e.cpb = w.cpb;
-    e.enc_cap = w.enc_cap;
-    e.dt = c.dt;
-    BsArgs b;
-    b.xm = w.xm;
-    b.vv = w.vv;
-    b.dP = w.dP;
-    b.xpre = w.xpre;
-    b.vpre = w.vpre;
-    b.rc = w.rc_cur;
-    b.goff = w.goff;
-    b.gmem = w.gmem;
-    b.big = w.bsbig;
-    b.bpos = w.bspos;
-    b.bmem = w.bsmem;
-    b.rc_w = w.rc_cur;
-    b.rad = w.rad;
-    b.sp = w.sp;
-    b.ids = w.ids;
-    b.dead = w.dead;
-    b.ev = w.ev;
-    b.st = w.st;
-    b.G = c.G;
-    b.Gm0 = c.mu;
-    b.dt = c.dt;
-    b.tol = c.bs_tol;
-    b.max_depth = c.bs_max_depth;
-    b.coll = c.coll;
-    b.ev_cap = w.ev_cap;
+    const EncArgs e = enc_args(w, c);
+    const BsArgs b = bs_args(w, c);
     const dim3 bs_grid(std::max(1, std::min(256, w.n / 2)));
     if (c.all_pairs) {
       // composed steps (not timed per kernel): every pair tested

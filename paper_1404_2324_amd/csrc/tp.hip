@@ -255,7 +255,7 @@ __device__ __forceinline__ void tp_list(const TpArgs& a, int64_t pos, int64_t k,
 }
 
 // One lane per particle.  Bound by FP64 issue (1600 vector instructions a
-// particle; 10^6 particles and 8 planets 65 us, where their 104 MB would take 13
+// particle; 10^6 particles and 8 planets 68 us, where their 104 MB would take 13
 // us).  A block's listed particles go to its own region of the list (which
 // the encounter report reads) and their positions, by one atomic per block, to
 // the step's list: that order does not matter, and it replaced a one-workgroup
