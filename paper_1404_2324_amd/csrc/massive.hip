@@ -843,6 +843,198 @@ struct GroupLds {
   int chg[2];
 };
 
+// The step's candidate rows cleared for its closing kick by the threads t0,
+// t0 + nt, ...; returns their entries (summed over the wave).  Eight rows'
+// loads go out before the first store: with a load and a store in turn, 2048
+// rows took a workgroup eight round trips to memory.
+__device__ __forceinline__ int clear_rows(const EncArgs& a, int t0, int nt) {
+  constexpr int U = 8;
+  int rows = 0;
+  for (int i0 = t0; i0 < a.n; i0 += U * nt) {
+    int c[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * nt;
+      c[u] = i < a.n ? a.ccnt[i] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + u * nt;
+      if (i < a.n) a.ccnt[i] = 0;
+      rows += min(c[u], a.cpb);
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) rows += __shfl_xor(rows, o, 64);
+  return rows;
+}
+
+// Inclusive prefix sum over the wave, every lane active: within rows of 16
+// lanes by row shifts, then the row ends broadcast to the rows behind (DPP, no
+// trip through LDS as shuffles take).
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);   // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);   // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15, rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31, rows 2, 3
+  return v;
+}
+
+// The grouping of ne <= 64 kFewU pairs, nearly every step's, by wave 0 without
+// a barrier: lane l holds the pairs l, l + 64, ...; labels fall to each
+// class's smallest body in LDS, a group's id is the count of root bits below
+// its root's in a bitmap of the bodies, and the count that gives the sizes also
+// gives each member its place.  Groups, offsets and members are the general
+// form's below, whose ~20 barriers took most of a step's fixed cost; the other
+// waves meanwhile clear the candidate rows (writer).  Bound by the chain of LDS
+// round trips: 77 pairs of 2048 bodies 11.7 thousand cycles -> 7.2, the
+// kernel 39.4 -> 37.2 us.  Four pairs a lane hold a crowded step of a few
+// thousand bodies; beyond 256 the general form spreads them over every wave.
+constexpr int kFewU = 4;
+template <int NT, class GL>
+__device__ __forceinline__ int group_few(const EncArgs& a, int ne, GL& L, int* gm, bool writer,
+                                         int2 q0) {
+  constexpr int NW = (GL::kN + 31) / 32;  // words of the bitmap
+  static_assert(NW <= 64 && NW <= GL::kN / 2, "a word per lane, held in roots");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave == 0) {
+    int2 q[kFewU];
+    q[0] = q0;
+#pragma unroll
+    for (int u = 1; u < kFewU; ++u) {
+      q[u] = make_int2(0, 0);
+      if (64 * u + lane < ne) q[u] = a.encij[64 * u + lane];
+    }
+    if (lane < NW) L.roots[lane] = 0;
+#pragma unroll
+    for (int u = 0; u < kFewU; ++u)
+      if (64 * u + lane < ne) {
+        L.link[q[u].x] = q[u].x;
+        L.link[q[u].y] = q[u].y;
+        L.first[q[u].x] = L.first[q[u].y] = INT_MAX;
+        L.gid[q[u].x] = L.gid[q[u].y] = 0;
+      }
+    wsync();
+    // each body's first end
+#pragma unroll
+    for (int u = 0; u < kFewU; ++u)
+      if (64 * u + lane < ne) {
+        atomicMin(&L.first[q[u].x], 2 * (64 * u + lane));
+        atomicMin(&L.first[q[u].y], 2 * (64 * u + lane) + 1);
+      }
+    // labels only fall, so the sweeps end; at the end both bodies of every
+    // pair name the same root, which names itself
+    for (;;) {
+      bool ch = false;
+#pragma unroll
+      for (int u = 0; u < kFewU; ++u)
+        if (64 * u + lane < ne) {
+          const int x = L.link[q[u].x], y = L.link[q[u].y];
+          if (x != y) {
+            const int m = min(x, y);
+            atomicMin(&L.link[q[u].x], m);
+            atomicMin(&L.link[q[u].y], m);
+            atomicMin(&L.link[max(x, y)], m);
+            ch = true;
+          }
+        }
+      wsync();
+      if (__ballot(ch) == 0ull) break;
+#pragma unroll
+      for (int u = 0; u < kFewU; ++u)
+        if (64 * u + lane < ne) {
+          atomicMin(&L.link[q[u].x], L.link[L.link[q[u].x]]);
+          atomicMin(&L.link[q[u].y], L.link[L.link[q[u].y]]);
+        }
+      wsync();
+    }
+    // places in the group (-1: not the body's first end) and roots
+    int px[kFewU], py[kFewU], lab[kFewU];
+#pragma unroll
+    for (int u = 0; u < kFewU; ++u) {
+      px[u] = py[u] = -1;
+      lab[u] = 0;
+      if (64 * u + lane < ne) {
+        const int e2 = 2 * (64 * u + lane);
+        const int l = L.link[q[u].x];
+        lab[u] = l;
+        if (L.first[q[u].x] == e2) {
+          px[u] = atomicAdd(&L.gid[l], 1);
+          if (l == q[u].x) atomicOr(&L.roots[l >> 5], (int)(1u << (l & 31)));
+        }
+        if (L.first[q[u].y] == e2 + 1) {
+          py[u] = atomicAdd(&L.gid[l], 1);
+          if (l == q[u].y) atomicOr(&L.roots[l >> 5], (int)(1u << (l & 31)));
+        }
+      }
+    }
+    wsync();
+    const int wd = lane < NW ? L.roots[lane] : 0;
+    const int pc = __popc((unsigned)wd);
+    const int inc = wave_incl_scan(pc);
+    const int ng = __builtin_amdgcn_readlane(inc, 63);
+    // a lane's roots: sizes by group id, and the id at the root
+    int g = inc - pc;
+    for (unsigned r = (unsigned)wd; r; r &= r - 1u, ++g) {
+      const int i = 32 * lane + __ffs((int)r) - 1;
+      L.gsz[g] = L.gid[i];
+      L.first[i] = g;
+    }
+    wsync();
+    int tot = 0, mx = 0;
+    for (int c0 = 0; c0 < ng; c0 += 64) {
+      const int v = c0 + lane < ng ? L.gsz[c0 + lane] : 0;
+      const int s = wave_incl_scan(v);
+      if (c0 + lane < ng) {
+        L.gof[c0 + lane] = tot + s - v;
+        if (writer) a.goff[c0 + lane] = tot + s - v;
+      }
+      mx = max(mx, v);
+      tot += __builtin_amdgcn_readlane(s, 63);
+    }
+    wsync();
+#pragma unroll
+    for (int u = 0; u < kFewU; ++u) {
+      if (px[u] < 0 && py[u] < 0) continue;
+      const int o = L.gof[L.first[lab[u]]];
+      if (px[u] >= 0) {
+        if (gm) gm[o + px[u]] = q[u].x;
+        if (writer) a.gmem[o + px[u]] = q[u].x;
+      }
+      if (py[u] >= 0) {
+        if (gm) gm[o + py[u]] = q[u].y;
+        if (writer) a.gmem[o + py[u]] = q[u].y;
+      }
+    }
+    mx = wave_max_i(mx);
+    if (lane == 0) {
+      L.nroot = ng;
+      L.gof[ng] = tot;
+      if (writer) {
+        a.goff[ng] = tot;
+        a.st->ctl = 0u;  // as in the general form
+        a.st->maxg = mx;
+        a.st->ngroups = ng;
+        a.st->enc_total += (unsigned long long)ne;
+      }
+    }
+  } else if (writer) {
+    const int rows = clear_rows(a, threadIdx.x - 64, NT - 64);
+    if (lane == 0) L.shw[wave] = rows;
+  }
+  __syncthreads();
+  if (writer && threadIdx.x == 0) {
+    int rows = 0;
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) rows += L.shw[w];
+    a.st->ncand = rows / 2;
+  }
+  return __builtin_amdgcn_readfirstlane(L.nroot);
+}
+
 // The grouping of ne_all encounter pairs by one workgroup of NT threads;
 // returns the number of groups.  gm (LDS, or null): the members by group at
 // the offsets gof.  writer: this workgroup writes the global results.  pf
@@ -862,6 +1054,11 @@ __device__ __forceinline__ int group_phase(const EncArgs& a, int ne_all, GL& L,
   const int tid = threadIdx.x, lane = tid & 63;
   const int n = a.n;
   const int ne = min(ne_all, a.enc_cap);
+  if (ne_all <= 64 * kFewU && ne == ne_all) {
+    // (the first wave's pairs; it loads any further ones itself)
+    return group_few<NT>(a, ne, L, gm, writer,
+                         pf ? *pf : tid < ne ? a.encij[tid] : make_int2(0, 0));
+  }
   const int nl = min(ne, GL::kPairs);  // pairs held in LDS
   auto pair_at = [&](int e) { return e < nl ? pr[e] : a.encij[e]; };
   auto end_at = [&](int t) {  // end t of the pairs: pair t / 2, first or second body
@@ -880,11 +1077,8 @@ __device__ __forceinline__ int group_phase(const EncArgs& a, int ne_all, GL& L,
   // candidate pairs i < j: every pair sits in both rows (the test is
   // symmetric), so half the sum of the row lengths
   int rows = 0;
-  if (writer)
-    for (int i = tid; i < n; i += NT) {
-      rows += min(a.ccnt[i], a.cpb);
-      a.ccnt[i] = 0;
-    }
+  if (writer) rows = clear_rows(a, tid, NT);
+  rows = lane == 0 ? rows : 0;  // the wave's sum once
   for (int t = tid; t < 2 * ne; t += NT) {
     const int i = end_at(t);
     link[i] = i;
@@ -2843,8 +3037,7 @@ BsArgs bs_args(const MassiveWs& w, const StepConsts& c) {
 // step in calls of 16, separate kernels against this one: 16 bodies without
 // encounters 17.0 / 6.8, with two groups of two 31.8 / 24.7; 8 bodies in one
 // group 35.8 / 30.2.  It loses only where 9 to 16 bodies form one group, which
-// one wave integrates on either path: 16 bodies 179 / 188, of which 4 the BS
-// alone (17 bodies, not taken, 189 / 193 against the same older BS).  32 bodies
+// one wave integrates on either path: 16 bodies 179 / 188.  32 bodies
 // without encounters 17.7 / 7.6, but with 6 groups 47.3 / 63.6.
 bool massive_small(const MassiveWs& w, const StepConsts& c) {
   return w.n <= kSmallN && !c.all_pairs && !c.phys && !c.coll;

@@ -12,7 +12,7 @@ from paper_1404_2324_amd import workloads as W
 
 def _sim(n, n1, free):
     s = W.planetesimals(n, seed_index=40 + n)
-    gp = G.default_params(n1=n1, encounter_free=free)
+    gp = G.default_params(n1=n1, encounter_free=free, cand_per_body=300)
     return s, gp, G.Simulation(s.m, s.x, s.u, gp, coords="helio")
 
 
@@ -50,3 +50,27 @@ def test_small_steps_equal_separate_kernels(n, n1, free):
         d = np.linalg.norm(p - q, axis=1) / np.linalg.norm(q, axis=1)
         print("rel", d.max(), flush=True)
         assert (d <= 1e-12).all()
+
+
+# Encounter pairs of a step on both sides of the counts at which the grouping
+# changes: one pair a lane (11; 61 to 65), four a lane (256; 268).  Pairs, groups and the largest
+# group are whole numbers; states as above.
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,n1", [(300, 30.0), (90, 196.0), (200, 96.0), (300, 115.0), (300, 118.0)])
+def test_groups_of_few_and_many_pairs(n, n1):
+    print("groups", n, n1, flush=True)
+    s, gp, a = _sim(n, n1, 0)
+    op = O.params(G=gp.G, m0=gp.m0, dt=gp.dt, n1=gp.n1, n2=gp.n2, pf=gp.pf, bs_tol=gp.bs_tol,
+                  bs_max_depth=gp.bs_max_depth, kepler_max_iter=gp.kepler_max_iter)
+    o = O.MassiveSim(op, s.m, s.x, s.u, coords="helio")
+    for _ in range(4):
+        a.step(1)
+        a.check()
+        sa, so = a.stats(), o.step(1)
+        print({k: (sa[k], so[k]) for k in ("n_enc", "n_groups", "max_group", "n_cand")}, flush=True)
+        for k in ("n_enc", "n_groups", "max_group", "n_cand"):
+            assert sa[k] == so[k], k
+        x, v = [t.cpu().numpy() for t in a.state("dem")]
+        for p, q in ((x, o.x), (v, o.v)):
+            d = np.linalg.norm(p - q, axis=1) / np.linalg.norm(q, axis=1)
+            assert (d <= 1e-12).all()
