@@ -111,29 +111,23 @@ __device__ __forceinline__ unsigned long long sys_lanes(int l) {
 __device__ __forceinline__ int kick_slot(int j) { return j + (j >> 5); }
 constexpr int kKickSlots = 66;
 
-// Partner jj of the lane's system: wave-uniform lane reads (PK = 1) or the
-// LDS tables (PK = 2).
+// Partner jj of the lane's system, from the LDS tables: every lane of the
+// system reads one address.  With one system per wave too: ten lane reads with
+// a variable index a partner, each waited for by its use, bound the kick there
+// (300 systems of up to 64 bodies, 32 steps: 1562 us with them, 1510 so).
 template <int PK>
 __device__ __forceinline__ void kick_partner(int jj, int hb, double x, double y, double z,
                                              double m, double rc, const double4* kp,
                                              const double* krc, double& xj, double& yj,
                                              double& zj, double& mj, double& rcj) {
-  if (PK == 1) {
-    xj = readlane_d(x, jj);
-    yj = readlane_d(y, jj);
-    zj = readlane_d(z, jj);
-    mj = readlane_d(m, jj);
-    rcj = readlane_d(rc, jj);
-  } else {
-    // kick_slot(hb + jj) = kick_slot(hb) + jj for jj < 32
-    const int t = kick_slot(hb) + jj;
-    const double4 pj = kp[t];
-    xj = pj.x;
-    yj = pj.y;
-    zj = pj.z;
-    mj = pj.w;
-    rcj = krc[t];
-  }
+  // kick_slot(hb + jj) = kick_slot(hb) + jj for jj < 32
+  const int t = PK == 1 ? jj : kick_slot(hb) + jj;
+  const double4 pj = kp[t];
+  xj = pj.x;
+  yj = pj.y;
+  zj = pj.z;
+  mj = pj.w;
+  rcj = krc[t];
 }
 
 // U consecutive partners jj0 .. jj0 + U - 1 (all below nloop), accumulated
@@ -143,7 +137,7 @@ __device__ __forceinline__ void kick_partner(int jj, int hb, double x, double y,
 // the changeover (Eqs. 4-5); mj (K ir^3 - dK ir^2) with K = 1, dK = 0 is
 // mj ir^3 exactly, so both paths round as the single formula does.  The
 // fused operations are spelled out, so that the roundings do not depend on
-// how the partner data arrive (lane reads or LDS).
+// how the compiler arranges them.
 template <int PK, int U>
 __device__ __forceinline__ void kick_chunk(int jj0, int nh, int lane, int hb, double x, double y,
                                            double z, double m, double rc, double pf2,
@@ -221,10 +215,9 @@ __device__ __forceinline__ void kick_chunk(int jj0, int nh, int lane, int hb, do
 // rc = 0 everywhere gives the Newtonian pair sum (K = 1, the encounter-free
 // map).  The system occupies lanes hb .. hb + nh - 1; partners are visited
 // in index order jj = 0 .. nh - 1 whatever PK, so both layouts give the same
-// sums.  One system per wave reads the partner by wave-uniform lane reads;
-// two systems per wave (nloop = the larger size, kp / krc: LDS tables of
-// kKickSlots entries) read it from LDS, where each half's lanes all read one
-// address.
+// sums.  kp, krc: LDS tables of kKickSlots entries, one per wave, written here
+// (nloop = the larger size of two systems per wave, whose halves each read one
+// address); called with the whole workgroup, one wave, active.
 template <int PK>
 __device__ __forceinline__ void sys_kick(int nloop, int nh, int lane, int hb, double x, double y,
                                          double z, double m, double rc, double G, double pf2,
@@ -232,12 +225,11 @@ __device__ __forceinline__ void sys_kick(int nloop, int nh, int lane, int hb, do
                                          unsigned long long& cand, double4* kp, double* krc) {
   ax = ay = az = 0.0;
   cand = 0ull;
-  if (PK == 2) {
-    __syncthreads();  // earlier reads of the tables are done
-    kp[kick_slot(lane)] = make_double4(x, y, z, m);
-    krc[kick_slot(lane)] = rc;
-    __syncthreads();
-  }
+  const int slot = PK == 1 ? lane : kick_slot(lane);
+  __syncthreads();  // earlier reads of the tables are done
+  kp[slot] = make_double4(x, y, z, m);
+  krc[slot] = rc;
+  __syncthreads();
   int jj = 0;
   for (; jj + 8 <= nloop; jj += 8)
     kick_chunk<PK, 8>(jj, nh, lane, hb, x, y, z, m, rc, pf2, want_cand, kp, krc, ax, ay, az,
@@ -380,8 +372,8 @@ __device__ __forceinline__ void put_event(const BatchArgs& a, int kind, int sys,
 template <int LB, int PK, bool PH>
 __global__ __launch_bounds__(64, LB) void k_batch(BatchArgs a) {
   __shared__ double mm[kBsPar], mrc[kBsPar], mR[kBsPar];
-  __shared__ double4 kp[PK == 2 ? kKickSlots : 1];
-  __shared__ double krc[PK == 2 ? kKickSlots : 1];
+  __shared__ double4 kp[kKickSlots];
+  __shared__ double krc[kKickSlots];
   __shared__ double hs[13][kKickSlots];  // pre-drift state, drifted state, radius
   __shared__ unsigned kh[PK][kKepBins];  // each system's drifts by iteration count
   const int lane = threadIdx.x;
@@ -843,6 +835,8 @@ __global__ __launch_bounds__(64) void k_batch_unpack(const double4* __restrict__
 // Candidates entering the first step: radii of the initial state and the
 // prechecker on the initial positions (Sec. 2.2).
 __global__ __launch_bounds__(64) void k_batch_prime(BatchArgs a) {
+  __shared__ double4 kp[kKickSlots];
+  __shared__ double krc[kKickSlots];
   const int s = blockIdx.x, lane = threadIdx.x;
   const int o = a.off[s], n = a.ss[s].nlive;
   const bool act = lane < n;
@@ -858,7 +852,7 @@ __global__ __launch_bounds__(64) void k_batch_prime(BatchArgs a) {
   double ax, ay, az;
   unsigned long long cand;
   sys_kick<1>(n, n, lane, 0, p.x, p.y, p.z, p.w, rc, a.G, a.pf2, !a.enc_free, ax, ay, az, cand,
-              nullptr, nullptr);
+              kp, krc);
   if (act) {
     a.cand[o + lane] = cand;
     a.encm[o + lane] = 0ull;
