@@ -17,6 +17,8 @@
 //                  per split of the partners
 //   k_pair_finish  per body: the splits added, the second Sun kick tau/2,
 //                  v += tau/2 a and the next radii
+// Systems of up to kSmallN bodies take all of it, several steps at once, in one
+// launch of one workgroup (k_small_steps).
 // Between steps the positions live in xs (the closing kick's output); x
 // holds them while a step runs.
 #include <hip/hip_ext.h>
