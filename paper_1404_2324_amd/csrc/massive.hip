@@ -2587,10 +2587,11 @@ __global__ __launch_bounds__(kEnW * 64) void k_energy_part(const double4* __rest
         const double4 pj = cur[u];
         const double dx = pj.x - p.x, dy = pj.y - p.y, dz = pj.z - p.z;
         const double r2 = dx * dx + dy * dy + dz * dz;
-        const bool z = r2 == 0.0;
         const double t = pj.w * rsqrt_nr(r2);
+        const bool z = t != t;  // the refined root of 0 or infinity
         s += z ? 0.0 : t;
-        // a body against itself adds nothing; two bodies at one place do
+        // a body against itself adds nothing; two bodies at one place or past
+        // 1e154 apart do, by the general root
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(z) != 0ull, 0))
           if (z && tj * 64 + q0 + u != i) s += pj.w / sqrt(r2);
       }
