@@ -186,7 +186,10 @@ __device__ __forceinline__ void accel_B(const HArgs& a, const Sys& S, const doub
       const double rcij = rc > rcj ? rc : rcj;
       double K, dK;
       chg(r, rcij, K, dK);
-      const double f = div_nr(K, r2 * r) - div_nr(dK, r2);
+      double f = div_nr(K, r2 * r) - div_nr(dK, r2);
+      // a body so far out that the cube leaves the short quotient's range: its
+      // term is nothing (below 1e-200)
+      f = r2 > 1e200 ? 0.0 : f;
       const double s = a.G * mj * f;
       acc[0] += s * d0;
       acc[1] += s * d1;

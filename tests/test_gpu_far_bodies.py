@@ -23,3 +23,27 @@ def test_energy_with_a_far_body(far):
     # a dozen terms of the size of the largest, each rounded a few times
     assert abs(E - Eo) <= 64 * 2.2e-16 * m[0]
     assert np.isfinite(L).all()
+
+
+# the same three bodies with and without a fourth one whose r^3 is in range, near
+# the largest double, above it
+@pytest.mark.gpu
+@pytest.mark.parametrize("far", [1e90, 5.5e102, 6e102, 1e120])
+def test_hybrid_adjoint_forward_with_a_far_body(far):
+    print("hybrid far", far, flush=True)
+    m = np.array([1e-6, 2e-6, 3e-6, 1e-9])
+    x = np.array([[1.0, 0, 0], [0, 2.0, 0], [0, 0, 3.0], [far, 0, 0]])
+    v = np.array([[0, 1.0, 0], [-0.7, 0, 0], [0.5, 0, 0], [0, 0, 0]])
+    out = []
+    for n in (3, 4):
+        sim = G.BatchedSimulation(np.array([0, n]), np.ones(1), m[:n], x[:n], v[:n],
+                                  G.default_params(), coords="dem")
+        sim.adj_forward(4, 2)
+        xT, vT = (t.cpu().numpy() for t in sim.state("dem"))
+        sim.check()
+        out.append((xT, vT))
+    (xa, va), (xb, vb) = out
+    # the far body adds less than a rounding to the others
+    assert np.abs(xb[:3] - xa).max() <= 1e-15 and np.abs(vb[:3] - va).max() <= 1e-15
+    # which it moves by the Sun kick alone, as all bodies
+    assert np.linalg.norm(xb[3] - x[3]) <= 1e-15 * far and np.abs(vb[3]).max() <= 1e-15
