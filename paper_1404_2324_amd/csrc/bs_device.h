@@ -23,32 +23,50 @@ constexpr int kBsMaxAttempts = 1 << 16;  // substep attempts per group and step
 
 // dv/dt of H_A for the lane's body: the fixed star plus the (1-K) part of the
 // group's pair terms (Eq. 1 gradient); other members' data by lane reads.
+// Partners go two by two: their terms are independent chains, computed without
+// branches (a far or absent partner's is set to zero).  Bound by that chain
+// (one wave on its SIMD): a partner at a time, with a branch at each test,
+// took 171 us a step for 16 bodies in one group and 192 for 17, this takes 137
+// and 149 (64 bodies 988 -> 802), the same bits.
 __device__ __forceinline__ void ha_accel(int sz, int lane, double x, double y,
                                          double z, double m, double rc,
                                          double G, double Gm0, double& ax,
                                          double& ay, double& az) {
+  constexpr int U = 2;
   const double r2 = x * x + y * y + z * z;
   const double ir = rsqrt_nr(r2);
   const double fs = -Gm0 * (ir * ir * ir);
   ax = fs * x;
   ay = fs * y;
   az = fs * z;
-  for (int j = 0; j < sz; ++j) {
-    const double xj = readlane_d(x, j), yj = readlane_d(y, j), zj = readlane_d(z, j);
-    const double mj = readlane_d(m, j), rcj = readlane_d(rc, j);
-    const double dx = xj - x, dy = yj - y, dz = zj - z;
-    const double q2 = dx * dx + dy * dy + dz * dz;
-    const double rij = fmax(rc, rcj);
-    // the term vanishes exactly beyond rc_ij (K = 1, K' = 0)
-    if (j != lane && q2 < rij * rij * (1.0 + 1e-12)) {
-      const double iq = rsqrt_nr(q2);
+  for (int j0 = 0; j0 < sz; j0 += U) {
+    double dx[U], dy[U], dz[U], q2[U], rij[U], mj[U];
+    bool near[U], any = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + u;  // at most 63: sz <= 64
+      dx[u] = readlane_d(x, j) - x;
+      dy[u] = readlane_d(y, j) - y;
+      dz[u] = readlane_d(z, j) - z;
+      mj[u] = readlane_d(m, j);
+      q2[u] = dx[u] * dx[u] + dy[u] * dy[u] + dz[u] * dz[u];
+      rij[u] = fmax(rc, readlane_d(rc, j));
+      // the term vanishes exactly beyond rc_ij (K = 1, K' = 0)
+      near[u] = j < sz && j != lane && q2[u] < rij[u] * rij[u] * (1.0 + 1e-12);
+      any = any || near[u];
+    }
+    if (__builtin_amdgcn_ballot_w64(any) == 0ull) continue;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double iq = rsqrt_nr(q2[u]);
       const double iq2 = iq * iq;
       double K, dK;
-      changeover(q2 * iq, rij, K, dK);
-      const double s = G * mj * ((1.0 - K) * iq2 * iq + dK * iq2);
-      ax += s * dx;
-      ay += s * dy;
-      az += s * dz;
+      changeover_clamped(q2[u] * iq, rij[u], rcp_nr(0.9 * rij[u]), K, dK);
+      double s = G * mj[u] * ((1.0 - K) * iq2 * iq + dK * iq2);
+      s = near[u] ? s : 0.0;
+      ax += s * dx[u];
+      ay += s * dy[u];
+      az += s * dz[u];
     }
   }
 }
