@@ -311,7 +311,7 @@ __device__ __forceinline__ int group_seq(const BatchArgs& a, int sz, unsigned lo
     rcb = 0.0;
     Rb = 0.0;
   }
-  const int r = bs_integrate(sz, lane, y, H, mb, rcb, a.G, Gm0, a.tol, a.max_depth, R, nsub, Rb,
+  const int r = bs_integrate<true>(sz, lane, y, H, mb, rcb, a.G, Gm0, a.tol, a.max_depth, R, nsub, Rb,
                              coll ? ckey : nullptr, cpos);
   const int rank = __popcll(M & ((1ull << lane) - 1ull));
 #pragma unroll

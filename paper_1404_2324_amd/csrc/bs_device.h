@@ -21,13 +21,23 @@ __device__ __forceinline__ void wsync() {
 constexpr int kBsCols = 8;
 constexpr int kBsMaxAttempts = 1 << 16;  // substep attempts per group and step
 
+// 1 - K with both roundings: K's last product may not fuse into it, as it could
+// not where K came out of a branch.
+__device__ __forceinline__ double one_minus(double K) {
+#pragma clang fp contract(off)
+  return 1.0 - K;
+}
+
 // dv/dt of H_A for the lane's body: the fixed star plus the (1-K) part of the
 // group's pair terms (Eq. 1 gradient); other members' data by lane reads.
 // Partners go two by two: their terms are independent chains, computed without
 // branches (a far or absent partner's is set to zero).  Bound by that chain
 // (one wave on its SIMD): a partner at a time, with a branch at each test,
 // took 171 us a step for 16 bodies in one group and 192 for 17, this takes 137
-// and 149 (64 bodies 988 -> 802), the same bits.
+// and 149 (64 bodies 988 -> 802).  FK: which product of the pair's weight fuses
+// into the other's sum; both forms are kept for the bits of their callers (deep
+// passages amplify a last bit).
+template <bool FK>
 __device__ __forceinline__ void ha_accel(int sz, int lane, double x, double y,
                                          double z, double m, double rc,
                                          double G, double Gm0, double& ax,
@@ -62,7 +72,8 @@ __device__ __forceinline__ void ha_accel(int sz, int lane, double x, double y,
       const double iq2 = iq * iq;
       double K, dK;
       changeover_clamped(q2[u] * iq, rij[u], rcp_nr(0.9 * rij[u]), K, dK);
-      double s = G * mj[u] * ((1.0 - K) * iq2 * iq + dK * iq2);
+      const double k1 = one_minus(K) * iq2;
+      double s = G * mj[u] * (FK ? fma(k1, iq, dK * iq2) : fma(dK, iq2, k1 * iq));
       s = near[u] ? s : 0.0;
       ax += s * dx[u];
       ay += s * dy[u];
@@ -73,11 +84,12 @@ __device__ __forceinline__ void ha_accel(int sz, int lane, double x, double y,
 
 // Gragg's modified midpoint rule over H with nsub substeps (one wave, one
 // body per lane).
+template <bool FK>
 __device__ __forceinline__ void mmid(int sz, int lane, const double y0[6], double H, int nsub,
                      double m, double rc, double G, double Gm0, double out[6]) {
   const double hs = H / nsub;
   double ym[6], yn[6], d[6];
-  ha_accel(sz, lane, y0[0], y0[1], y0[2], m, rc, G, Gm0, d[3], d[4], d[5]);
+  ha_accel<FK>(sz, lane, y0[0], y0[1], y0[2], m, rc, G, Gm0, d[3], d[4], d[5]);
   d[0] = y0[3];
   d[1] = y0[4];
   d[2] = y0[5];
@@ -87,7 +99,7 @@ __device__ __forceinline__ void mmid(int sz, int lane, const double y0[6], doubl
     yn[c] = y0[c] + hs * d[c];
   }
   for (int s = 1; s < nsub; ++s) {
-    ha_accel(sz, lane, yn[0], yn[1], yn[2], m, rc, G, Gm0, d[3], d[4], d[5]);
+    ha_accel<FK>(sz, lane, yn[0], yn[1], yn[2], m, rc, G, Gm0, d[3], d[4], d[5]);
     d[0] = yn[3];
     d[1] = yn[4];
     d[2] = yn[5];
@@ -98,7 +110,7 @@ __device__ __forceinline__ void mmid(int sz, int lane, const double y0[6], doubl
       yn[c] = t;
     }
   }
-  ha_accel(sz, lane, yn[0], yn[1], yn[2], m, rc, G, Gm0, d[3], d[4], d[5]);
+  ha_accel<FK>(sz, lane, yn[0], yn[1], yn[2], m, rc, G, Gm0, d[3], d[4], d[5]);
   d[0] = yn[3];
   d[1] = yn[4];
   d[2] = yn[5];
@@ -117,13 +129,14 @@ __device__ __forceinline__ double relerr3(const double* A, const double* B) {
 // extrapolation in h^2 kept in LDS (R[col][comp][lane]), accepted at the first
 // column k >= 2 whose per-body relative error (max over the group) is within
 // tol.  Returns true and the extrapolated state in y on success.
+template <bool FK>
 __device__ __forceinline__ bool bs_attempt(int sz, int lane, double y[6], double H, double m,
                            double rc, double G, double Gm0, double tol,
                            double (*R)[6][64]) {
   for (int k = 0; k < kBsCols; ++k) {
     const int nk = 2 * (k + 1);
     double t[6];
-    mmid(sz, lane, y, H, nk, m, rc, G, Gm0, t);
+    mmid<FK>(sz, lane, y, H, nk, m, rc, G, Gm0, t);
     for (int j = 1; j <= k; ++j) {
       const double ratio = (double)nk / (double)(2 * (k - j + 1));
       const double den = ratio * ratio - 1.0;
@@ -175,6 +188,7 @@ __device__ __forceinline__ bool pair_touches(double h, const double o[6], const 
 // that touches, the integration stops at the start of that substep and
 // returns 1 with a * 64 + b in *ckey and the covered part of [0, H] in *cpos
 // (units of H / 2^D).
+template <bool FK = false>
 __device__ __forceinline__ int bs_integrate(int sz, int lane, double y[6], double H, double m,
                             double rc, double G, double Gm0, double tol,
                             int D, double (*R)[6][64], long long* nsub, double Rb = 0.0,
@@ -189,7 +203,7 @@ __device__ __forceinline__ int bs_integrate(int sz, int lane, double y[6], doubl
     double yt[6];
 #pragma unroll
     for (int c = 0; c < 6; ++c) yt[c] = y[c];
-    if (bs_attempt(sz, lane, yt, ldexp(H, -d), m, rc, G, Gm0, tol, R)) {
+    if (bs_attempt<FK>(sz, lane, yt, ldexp(H, -d), m, rc, G, Gm0, tol, R)) {
       if (coll) {
         const double h = ldexp(H, -d);
         int best = INT_MAX;

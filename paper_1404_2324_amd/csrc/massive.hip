@@ -1451,17 +1451,20 @@ struct BsXchg {
 // once from the same start.  The first accepted slot in sequential order
 // wins; its state reaches every wave through LDS (each wave writes its own
 // beside its slot, so one barrier serves a round), and the waves, holding the
-// same state, position and depth, go on together.  The substeps taken and
-// their results are those of the one-wave bs_integrate_par.
+// same state, position and depth, go on together.  Without `all` the calling
+// wave does it alone, as the others do with groups of their own.  The substeps
+// taken and their results are those of the one-wave bs_integrate_par.
 template <int P>
 __device__ __forceinline__ int bs_integrate_mw(int sz, double y[6], double H,
                                                const ParBody<P>& Q, double G, double Gm0,
-                                               double tol, int D, long long* nsub, BsXchg& X) {
+                                               double tol, int D, long long* nsub, BsXchg& X,
+                                               bool all) {
   constexpr int S = kBsPar / P;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int b = par_memb<P>(lane);
-  const int c = par_col<P>(lane), s = wave * S + lane / (kBsPar * P);
+  const int s0 = all ? wave * S : 0, S1 = all ? kBsWaves * S : S;  // the wave's slots, all slots
+  const int c = par_col<P>(lane), s = s0 + lane / (kBsPar * P);
   // the substeps of every depth are this one scaled by a power of two (exact)
   const double hn = H / (2 * (c + 1));
   double wj[kBsCols];
@@ -1473,31 +1476,36 @@ __device__ __forceinline__ int bs_integrate_mw(int sz, double y[6], double H,
   int d = 0, attempts = 0;
   while (pos < total) {
     if (++attempts > kBsMaxAttempts) return -1;
-    const int smax = min(kBsWaves * S, D - d + 1);  // never beyond the depth limit
+    const int smax = min(S1, D - d + 1);  // never beyond the depth limit
     const int buf = attempts & 1;
     double yt[6];
 #pragma unroll
     for (int q = 0; q < 6; ++q) yt[q] = y[q];
     int gs = INT_MAX;
-    if (wave * S < smax) {
+    if (s0 < smax) {
       const int sa = bs_round_par<P, false>(sz, yt, ldexp(hn, -(d + s)), Q, G, Gm0, tol, wj, mid);
-      if (sa >= 0 && wave * S + sa < smax) {
-        gs = wave * S + sa;
+      if (sa >= 0 && s0 + sa < smax) {
+        gs = s0 + sa;
         if (lane == par_lane<P>(0, 0, b)) {
 #pragma unroll
           for (int q = 0; q < 6; ++q) X.y[buf][wave][b][q] = yt[q];
         }
       }
     }
-    if (lane == 0) X.gs[buf][wave] = gs;
-    __syncthreads();
-    int best = X.gs[buf][0];
+    int best = gs;
+    if (all) {
+      if (lane == 0) X.gs[buf][wave] = gs;
+      __syncthreads();
 #pragma unroll
-    for (int w = 1; w < kBsWaves; ++w) best = min(best, X.gs[buf][w]);
+      for (int w = 0; w < kBsWaves; ++w) best = min(best, X.gs[buf][w]);
+    } else {
+      wsync();
+    }
     best = __builtin_amdgcn_readfirstlane(best);
     if (best != INT_MAX) {
+      const int w = all ? best / S : wave;
 #pragma unroll
-      for (int q = 0; q < 6; ++q) y[q] = X.y[buf][best / S][b][q];
+      for (int q = 0; q < 6; ++q) y[q] = X.y[buf][w][b][q];
       d += best;
       ++*nsub;
       pos += 1ll << (D - d);
@@ -1511,17 +1519,17 @@ __device__ __forceinline__ int bs_integrate_mw(int sz, double y[6], double H,
 }
 
 // Main-mode group of sz <= P members without collisions (sorted indices in
-// mem; masses and radii staged in mm, mrc), on all waves of the workgroup:
-// start from the pre-drift copy, integrate, wave 0 writes back; returns the
-// BS status and, in wave 0, per member lane, its momentum change
-// m (v_BS - v_drift).
+// mem; masses and radii staged in mm, mrc), on all waves of the workgroup or on
+// the calling one: start from the pre-drift copy, integrate, wave 0 (the wave)
+// writes back; returns the BS status and, in that wave, per member lane, its
+// momentum change m (v_BS - v_drift).
 template <int P>
 __device__ __forceinline__ int bs_member_group(const BsArgs& a, int sz, const int* mem,
                                                double* mm, double* mrc, BsXchg& X,
-                                               long long* nsub, double& dpx, double& dpy,
-                                               double& dpz) {
+                                               long long* nsub, bool all, double& dpx,
+                                               double& dpy, double& dpz) {
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool lead = !all || __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0;
   const int b = par_memb<P>(lane);
   const int id = b < sz ? mem[b] : -1;
   // every load the group needs is issued at once: the members' masses and
@@ -1544,15 +1552,18 @@ __device__ __forceinline__ int bs_member_group(const BsArgs& a, int sz, const in
     y[4] = q.y;
     y[5] = q.z;
   }
-  if (ml >= 0 && wave == 0) {
+  if (ml >= 0 && lead) {
     mm[lane] = mw;
     mrc[lane] = rcw;
   }
-  __syncthreads();
+  if (all)
+    __syncthreads();
+  else
+    wsync();
   const ParBody<P> Q = par_body<P>(sz, mm, mrc);
-  const int r = bs_integrate_mw<P>(sz, y, a.dt, Q, a.G, a.Gm0, a.tol, a.max_depth, nsub, X);
+  const int r = bs_integrate_mw<P>(sz, y, a.dt, Q, a.G, a.Gm0, a.tol, a.max_depth, nsub, X, all);
   dpx = dpy = dpz = 0.0;
-  if (wave == 0 && lane == par_lane<P>(0, 0, b) && id >= 0) {  // one lane per member writes
+  if (lead && lane == par_lane<P>(0, 0, b) && id >= 0) {  // one lane per member writes
     const double m = mm[b];
     dpx = m * (y[3] - vo.x);
     dpy = m * (y[4] - vo.y);
@@ -1825,6 +1836,45 @@ struct BsLds {
   BsXchg X;
 };
 
+// One group of up to kBsPar members without collisions on all waves of the
+// workgroup or on the calling one: members sorted ascending, integrated, and the
+// group's momentum change written by wave 0 (the wave).
+__device__ __forceinline__ void bs_group_few(const BsArgs& a, const int* gmem, int g, int o,
+                                             int sz, int* mem, double* mm, double* mrc, BsXchg& X,
+                                             long long* nsub, bool all) {
+  const int lane = threadIdx.x & 63;
+  const bool lead = !all || __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0;
+  // every wave ranks the members; one writes them in order
+  const int my = lane < sz ? gmem[o + lane] : INT_MAX;
+  int rank = 0;
+  for (int q = 0; q < sz; ++q) rank += (__builtin_amdgcn_readlane(my, q) < my) ? 1 : 0;
+  if (lead && lane < sz) mem[rank] = my;
+  if (all)
+    __syncthreads();
+  else
+    wsync();
+  double dpx, dpy, dpz;
+  int r;
+  if (sz <= 2)
+    r = bs_member_group<2>(a, sz, mem, mm, mrc, X, nsub, all, dpx, dpy, dpz);
+  else if (sz <= 4)
+    r = bs_member_group<4>(a, sz, mem, mm, mrc, X, nsub, all, dpx, dpy, dpz);
+  else
+    r = bs_member_group<8>(a, sz, mem, mm, mrc, X, nsub, all, dpx, dpy, dpz);
+  if (!lead) return;
+  if (r != 0 && lane == 0) atomicOr(&a.st->flags, F_BS);
+  // the group's momentum change for the second Sun kick (fixed lane order)
+  dpx = wave_sum(dpx);
+  dpy = wave_sum(dpy);
+  dpz = wave_sum(dpz);
+  if (lane == 0) {
+    a.dP[4 * g + 0] = dpx;
+    a.dP[4 * g + 1] = dpy;
+    a.dP[4 * g + 2] = dpz;
+    a.dP[4 * g + 3] = 0.0;
+  }
+}
+
 // The ng groups (offsets goff[0 .. ng], members gmem at those offsets, in
 // global memory or LDS) on the workgroups of the grid, one group at a time
 // per workgroup (grid-stride): members sorted ascending, state reset to the
@@ -1834,43 +1884,14 @@ struct BsLds {
 // member with the columns in sequence, or the collision path).
 __device__ __forceinline__ void bs_groups(const BsArgs& a, int ng, const int* goff,
                                           const int* gmem, BsLds& L) {
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   long long nsub = 0;
   for (int g = blockIdx.x; g < ng; g += gridDim.x) {
     const int o = goff[g];
     const int sz = goff[g + 1] - o;
-    if (!a.coll && sz <= kBsPar) {
-      // every wave ranks the members; wave 0 writes them in order
-      const int my = lane < sz ? gmem[o + lane] : INT_MAX;
-      int rank = 0;
-      for (int q = 0; q < sz; ++q) rank += (__builtin_amdgcn_readlane(my, q) < my) ? 1 : 0;
-      if (wave == 0 && lane < sz) L.mem[rank] = my;
-      __syncthreads();
-      double dpx, dpy, dpz;
-      int r;
-      if (sz <= 2)
-        r = bs_member_group<2>(a, sz, L.mem, L.mm, L.mrc, L.X, &nsub, dpx, dpy, dpz);
-      else if (sz <= 4)
-        r = bs_member_group<4>(a, sz, L.mem, L.mm, L.mrc, L.X, &nsub, dpx, dpy, dpz);
-      else
-        r = bs_member_group<8>(a, sz, L.mem, L.mm, L.mrc, L.X, &nsub, dpx, dpy, dpz);
-      if (wave == 0) {
-        if (r != 0 && lane == 0) atomicOr(&a.st->flags, F_BS);
-        // the group's momentum change for the second Sun kick (fixed lane order)
-        dpx = wave_sum(dpx);
-        dpy = wave_sum(dpy);
-        dpz = wave_sum(dpz);
-        if (lane == 0) {
-          a.dP[4 * g + 0] = dpx;
-          a.dP[4 * g + 1] = dpy;
-          a.dP[4 * g + 2] = dpz;
-          a.dP[4 * g + 3] = 0.0;
-        }
-      }
-    } else if (wave == 0) {
+    if (!a.coll && sz <= kBsPar)
+      bs_group_few(a, gmem, g, o, sz, L.mem, L.mm, L.mrc, L.X, &nsub, true);
+    else if (threadIdx.x < 64)
       bs_group_one(a, gmem, g, o, sz, L.mem, L.mm, L.mrc, L.mR, L.R, &nsub);
-    }
     // the group's LDS (mem, mm, mrc, mR, R, X) is free for the next one
     __syncthreads();
   }
@@ -1925,7 +1946,8 @@ __global__ __launch_bounds__(64 * kBsWaves, LB) void k_group_bs(EncArgs e, BsArg
 // them), so both give the same bits.  The candidate rows live as bit masks and
 // go back to the table at the end.
 constexpr int kSmallN = 16;
-constexpr int kSmallW = 4;  // waves
+constexpr int kSmallW = 4;      // waves
+constexpr int kSmallSplit = 3;  // groups from which each wave takes its own
 static_assert(kSmallW == kBsWaves, "the workgroup integrates the groups");
 
 struct SmallArgs {
@@ -1946,7 +1968,39 @@ struct SmallLds {
   unsigned near[kSmallN / 2][kSmallN];  // candidates among the two partners
   unsigned kh[kKepBins];
   int ne;
+  int mem[kSmallW][kSmallN];  // a wave's own group
+  double mm[kSmallW][kBsPar], mrc[kSmallW][kBsPar];
 };
+
+// The groups of a small system's step by one workgroup: one or two in turn on
+// all waves, as bs_groups does; from kSmallSplit on each wave takes groups of
+// its own, with the same substeps (of so few bodies at most one group has more
+// than kBsPar members, which always take one wave).  In turn on all waves, five
+// groups of 16 bodies cost 57 us a step against 45 by the separate kernels.
+__device__ __forceinline__ void bs_groups_small(const BsArgs& a, int ng, SmallLds& L) {
+  static_assert(2 * (kBsPar + 1) > kSmallN, "one set of large-group records");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool all = ng < kSmallSplit;
+  BsLds& B = L.g.b;
+  const int *goff = L.g.g.gof, *gm = L.g.gm;
+  long long nsub = 0;
+  for (int g = all ? 0 : wave; g < ng; g += all ? 1 : kSmallW) {
+    const int o = goff[g];
+    const int sz = goff[g + 1] - o;
+    if (sz > kBsPar) {
+      if (!all || wave == 0)
+        bs_group_one(a, gm, g, o, sz, B.mem, B.mm, B.mrc, B.mR, B.R, &nsub);
+    } else {
+      const int w = all ? 0 : wave;
+      bs_group_few(a, gm, g, o, sz, L.mem[w], L.mm[w], L.mrc[w], B.X, &nsub, all);
+    }
+    if (all) __syncthreads();  // the group's LDS is free for the next one
+  }
+  if (!all) __syncthreads();
+  if (lane == 0 && (wave == 0 || !all) && nsub > 0)
+    atomicAdd(&a.st->bs_sub, (unsigned long long)nsub);
+}
 
 __global__ __launch_bounds__(64 * kSmallW) void k_small_steps(SmallArgs A) {
   __shared__ SmallLds L;
@@ -2124,11 +2178,13 @@ __global__ __launch_bounds__(64 * kSmallW) void k_small_steps(SmallArgs A) {
     __syncthreads();
     const int ne = __builtin_amdgcn_readfirstlane(L.ne);
     int ng = 0;
-    if (ne > 0) {
+    // (unlikely: the groups' registers are moved in and out here and not in every
+    // step)
+    if (__builtin_expect(ne > 0, 0)) {
       // (the row counts it sums for st->ncand and clears are the table's, not
       // these steps': both are set from the masks)
       ng = group_phase<64 * kSmallW>(e, ne, L.g.g, L.g.gm, true);
-      bs_groups(A.b, ng, L.g.g.gof, L.g.gm, L.g.b);
+      bs_groups_small(A.b, ng, L);
       if (w0) {
         if (act) {
           p = o.xm[i];
