@@ -140,6 +140,7 @@ __device__ __forceinline__ bool seg_acc(double G, const Lane<SB, PL>& L, double 
                                         double& az) {
   bool close = false;
   ax = ay = az = 0.0;
+  if constexpr (SB == 1) return close;  // a body alone
   constexpr int U = Lane<SB, PL>::UNROLL;
 #pragma unroll U
   for (int t = 0; t < Lane<SB, PL>::NT; ++t) {
@@ -168,7 +169,7 @@ __device__ __forceinline__ void free_step(const AdjArgs& a, const Lane<SB, PL>& 
                                           double& vy, double& vz, double x2[3], double v1[3],
                                           double& sK, unsigned& fl) {
   double ax, ay, az, rc2 = 0.0;
-  if (CLOSE) {
+  if (CLOSE && SB > 1) {
     // Eq. (6), squared; n1 (m / 3 m0)^(1/3) is the lane's constant cb
     const double r2 = x * x + y * y + z * z, vv = vx * vx + vy * vy + vz * vz;
     const double ir = rsqrt_nr(r2);
@@ -215,8 +216,13 @@ __device__ __forceinline__ double far_x(const Lane<SB, PL>& L) {
   return 1.0e3 + L.base + L.b;
 }
 
-template <int SB, int PL>
-__global__ __launch_bounds__(64) void k_adj_fwd(AdjArgs a) {
+// ONE: at most one wave on a SIMD.  Up to 1024 waves there is a SIMD for each,
+// but two that hold few registers may be put on one, and this kernel's waves
+// wait too little to share it: 40000 systems of one body, 64 steps, 100 us
+// without and 80 so, 24000 of two 151 and 118.
+template <int SB, int PL, bool ONE = false>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, ONE ? 1 : 8))) void
+k_adj_fwd(AdjArgs a) {
   const Lane<SB, PL> L = lane_of<SB, PL>(a);
   double x = far_x(L), y = 0.0, z = 0.0, vx = 0.0, vy = 0.0, vz = 0.0;
   if (L.act) {
@@ -428,13 +434,18 @@ AdjArgs adj_args(const BatchWs& b, const StepConsts& c, int T, int K, double* ck
 
 // The layout for nsys systems of sb bodies' lanes: the partner lanes that
 // shorten a step's chain, up to the number of waves where their copies' work
-// costs as much.  Systems of 8, 64 steps forward / backward in us, spread
-// against one lane per body (205 / 430 from 1024 to 8192 systems): 1024 systems
-// 121 / 246, 2048 175 / 378, 3072 286 / 562; systems of 16 at 3072: 388 / 815
-// against 406 / 813, of 32: 940 / 2454 against 983 / 2766.
+// costs as much.  64 steps forward / backward in us, spread against one lane
+// per body.  2 bodies, where the chain is short already: 4096 systems (256
+// waves) 93 / 181 against 104 / 200, 8192 103 / 200 against 105 / 205, 12000
+// 132 / 208 against 114 / 227, 20000 137 / 282 against 117 / 232.  4 bodies:
+// 4096 systems (1024 waves) 112 / 219 against 135 / 268, 5000 145 / 299 against
+// 145 / 291, 8192 156 / 323 against 150 / 298.  8 bodies: 1024 systems (1024
+// waves) 122 / 254 against 194 / 389, 2048 172 / 380 against 195 / 402.  16 bodies
+// at 3072 systems (waves): 308 / 790 against 397 / 800, 32: 779 / 2379 against 922 /
+// 2730 (at 2048 594 / 1642 against 722 / 1457).
 template <int SB>
 void adj_launch(const AdjArgs& a, bool bwd, hipStream_t s) {
-  constexpr int kSpread = SB <= 8 ? 2048 : 3072;  // waves
+  constexpr int kSpread = SB <= 2 ? 512 : SB <= 4 ? 1024 : SB <= 8 ? 2048 : 3072;  // waves
   constexpr int PL = SB < 64 / SB ? SB : 64 / SB;
   const int per = 64 / (SB * PL);  // systems per wave, spread
   const int ws = (a.nsys + per - 1) / per;
@@ -448,6 +459,8 @@ void adj_launch(const AdjArgs& a, bool bwd, hipStream_t s) {
     const dim3 g((a.nsys + 64 / SB - 1) / (64 / SB));
     if (bwd)
       hipLaunchKernelGGL((k_adj_bwd<SB, 1>), g, blk, 0, s, a);
+    else if (SB <= 4 && g.x <= 1024)
+      hipLaunchKernelGGL((k_adj_fwd<SB, 1, SB <= 4>), g, blk, 0, s, a);
     else
       hipLaunchKernelGGL((k_adj_fwd<SB, 1>), g, blk, 0, s, a);
   }
