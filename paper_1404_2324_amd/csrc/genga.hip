@@ -74,7 +74,7 @@ size_t ws_bytes(int mode, const genga_params& p, int nm, int64_t ntp, int nsys =
                 int64_t nbod = 0) {
   if (mode == GENGA_TEST) {
     TpWs t;
-    return align256(massive_ws_bytes(nm, p, true)) + tp_carve(t, ntp, nm, nullptr);
+    return align256(massive_ws_bytes(nm, p, true)) + tp_carve(t, ntp, nm, p.encounter_free, nullptr);
   }
   if (mode == GENGA_BATCH) {
     BatchWs b;
@@ -129,13 +129,7 @@ static void drop_graphs(genga_ctx* ctx) {
 
 // nsteps steps of test-particle mode on the capture stream, each step's
 // refinement beside the next step on a second branch (tp.hip), which the
-// stream joins before its end.  With few particles the refinement is short and
-// the two passes over the queue and the branch cost more than it: one branch.
-// us a step in graphs of 16, two branches against one: 10^6 particles and 8
-// planets 215 against 289 (310 before, with a one-workgroup scan of the lists),
-// 10^5 152 / 168, 10^4 98 / 114 and 93 / 104 (two draws), 3001 particles and 3
-// planets 84 / 94 and 69 / 49, 1000 particles 85 / 79.
-constexpr int64_t kTpOverlap = 8192;
+// stream joins before its end.
 static hipError_t record_tp_steps(genga_ctx* ctx, int nsteps, std::vector<hipEvent_t>& ev) {
   static_assert(kGraphSteps <= kTpSlots, "one planet slot per step of a graph");
   hipStream_t s = ctx->cap, sr = ctx->side;
@@ -148,7 +142,7 @@ static hipError_t record_tp_steps(genga_ctx* ctx, int nsteps, std::vector<hipEve
     ev.push_back(q);
     return ok(hipEventRecord(q, from)) && ok(hipStreamWaitEvent(to, q, 0));
   };
-  const bool side = nsteps > 1 && !ctx->c.encounter_free && ctx->t.ntp >= kTpOverlap;
+  const bool side = nsteps > 1 && tp_two_branches(ctx->t.ntp, ctx->c.encounter_free);
   for (int k = 0; k < nsteps; ++k) {
     const bool defer = side && k + 1 < nsteps;
     int* cnt = ctx->t.slot[k].cnt;
@@ -457,7 +451,7 @@ int genga_init(genga_ctx** out, int mode, const genga_params* p, int n_massive, 
   ctx->stream = (hipStream_t)stream;
   const bool tp = mode == GENGA_TEST;
   const size_t moff = align256(massive_carve(ctx->w, n_massive, *p, d_workspace, tp));
-  if (tp) tp_carve(ctx->t, n_test, n_massive, (char*)d_workspace + moff);
+  if (tp) tp_carve(ctx->t, n_test, n_massive, p->encounter_free, (char*)d_workspace + moff);
   int rc = GENGA_OK;
   if (hipStreamCreateWithFlags(&ctx->cap, hipStreamNonBlocking) != hipSuccess) rc = GENGA_EHIP;
   if (rc == GENGA_OK &&

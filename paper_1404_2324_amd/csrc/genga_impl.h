@@ -143,10 +143,12 @@ struct TpWs {
   double* x;            // [3][ntp]
   double* v;            // [3][ntp]
   unsigned* mask;       // candidate planets per particle
-  TpLists lists[2];     // used in turn by the steps of a graph
+  // With the second branch (tp_two_branches) two lists, used in turn by the steps
+  // of a graph, and a slot for each step; otherwise all of them the same one.
+  TpLists lists[2];
   TpSlot slot[kTpSlots];
   int last;             // the lists of the last step taken
-  unsigned char* busy;  // particles in refinement, left out by the next main pass
+  unsigned char* busy;  // particles in refinement, left out by the next main pass (or null)
   double* enc_d2;       // Hermite minimum of each encounter [nm][ntp]
   double* enc_rc2;      // its threshold r_crit,ij^2 [nm][ntp]
   int nm;               // massive bodies (stride of enc_d2, enc_rc2)
@@ -253,7 +255,9 @@ hipError_t accel_noalloc_run(const StepConsts& c, int n, const double* m, const 
                              const double* rc, double* acc, hipStream_t s);
 
 // ---- test-particle mode (tp.hip) --------------------------------------------
-size_t tp_carve(TpWs& t, int64_t ntp, int nm, void* base);
+// Whether a graph of several steps may run the refinement on a branch of its own.
+bool tp_two_branches(int64_t ntp, int encounter_free);
+size_t tp_carve(TpWs& t, int64_t ntp, int nm, int encounter_free, void* base);
 // The last step's particle-planet encounters (particle, planet, d2, rc2),
 // unsorted (synchronising).
 struct TpEnc {
