@@ -361,10 +361,14 @@ __global__ __launch_bounds__(64) void k_tp_late(TpArgs a, const double4* __restr
   }
   const double P2x = a.P2[0], P2y = a.P2[1], P2z = a.P2[2];
   const TpPlanets pl = {px0, pfin, prc};
-  // a few particles per wave: the queue is short, and a wave takes every
-  // branch that one of its particles needs
-  if (threadIdx.x >= kTpLateLanes) return;
-  for (int q = blockIdx.x * kTpLateLanes + threadIdx.x; q < nq; q += gridDim.x * kTpLateLanes) {
+  // a few particles per wave while the queue is short, since a wave takes every
+  // branch that one of its particles needs; with more than one each for those
+  // lanes every lane, since then the passes one after another cost more (8 steps
+  // of 100000 particles of which half meet a planet 1961 us with four lanes,
+  // 1717 so; 300000, a quarter of them, 1612 and 1520)
+  const int nl = nq > (int)gridDim.x * kTpLateLanes ? 64 : kTpLateLanes;
+  if ((int)threadIdx.x >= nl) return;
+  for (int q = blockIdx.x * nl + threadIdx.x; q < nq; q += gridDim.x * nl) {
     const int64_t k = a.pidx[a.prq[q]];
     const TpListed L = tp_particle(a, pl, k, P1x, P1y, P1z, P2x, P2y, P2z, sp, kh);
     if (L.it == 0) continue;  // removed in that refinement
