@@ -229,7 +229,7 @@ constexpr int kSlotPairs = 3;  // the pair kernel's slot
 hipError_t massive_step(const MassiveWs& w, const StepConsts& c, hipStream_t s,
                         const hipEvent_t* kev = nullptr, int* tpcnt = nullptr);
 // nsteps steps of a small system in one launch, when massive_small says that it
-// takes them; the same results as massive_step, bit for bit.
+// takes them; massive_step's operations in the same order (equal to rounding).
 bool massive_small(const MassiveWs& w, const StepConsts& c);
 hipError_t massive_small_steps(const MassiveWs& w, const StepConsts& c, int nsteps, hipStream_t s);
 hipError_t massive_energy(const MassiveWs& w, const StepConsts& c, double* dE,

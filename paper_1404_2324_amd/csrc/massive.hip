@@ -1444,26 +1444,52 @@ struct BsXchg {
   double y[2][kBsWaves][kBsPar][6];   // its state per member
 };
 
-// Binary refinement over [0, H] of a group of sz <= P members by the
-// kBsWaves waves of the workgroup: in each round wave w tries the depths
-// d + w S .. d + w S + S - 1 (S = kBsPar / P per wave, as bs_round_par lays
-// them out), so that kBsWaves S halvings of the substep are attempted at
-// once from the same start.  The first accepted slot in sequential order
+// The waves that integrate one group together: all of the workgroup's, one, or
+// some (which wait for each other by counting arrivals in LDS: the waves of a
+// workgroup are all resident, and every wave of a team makes the same waits,
+// since all of them hold the same state).
+struct BsTeam {
+  int w0, nw;   // first wave, waves
+  int* cnt;     // arrivals, 0 at the start (teams of some of the waves)
+  int due;
+  __device__ __forceinline__ int rank() const {
+    return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) - w0;
+  }
+  __device__ __forceinline__ void sync() {
+    if (nw == kBsWaves) {
+      __syncthreads();
+    } else if (nw == 1) {
+      wsync();
+    } else {
+      due += nw;
+      wsync();  // this wave's accesses are done
+      if ((threadIdx.x & 63) == 0)
+        __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+      while (__hip_atomic_load(cnt, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < due)
+        __builtin_amdgcn_s_sleep(1);
+      wsync();
+    }
+  }
+};
+
+// Binary refinement over [0, H] of a group of sz <= P members by the nw waves
+// of a team: in each round its wave w tries the depths d + w S .. d + w S + S -
+// 1 (S = kBsPar / P per wave, as bs_round_par lays them out), so that nw S
+// halvings of the substep are attempted at once from the same start.  The first accepted slot in sequential order
 // wins; its state reaches every wave through LDS (each wave writes its own
 // beside its slot, so one barrier serves a round), and the waves, holding the
-// same state, position and depth, go on together.  Without `all` the calling
-// wave does it alone, as the others do with groups of their own.  The substeps
-// taken and their results are those of the one-wave bs_integrate_par.
+// same state, position and depth, go on together.  The substeps taken and
+// their results are those of the one-wave bs_integrate_par.
 template <int P>
 __device__ __forceinline__ int bs_integrate_mw(int sz, double y[6], double H,
                                                const ParBody<P>& Q, double G, double Gm0,
                                                double tol, int D, long long* nsub, BsXchg& X,
-                                               bool all) {
+                                               BsTeam& T) {
   constexpr int S = kBsPar / P;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int b = par_memb<P>(lane);
-  const int s0 = all ? wave * S : 0, S1 = all ? kBsWaves * S : S;  // the wave's slots, all slots
+  const int s0 = T.rank() * S, S1 = T.nw * S;  // the wave's slots, all slots
   const int c = par_col<P>(lane), s = s0 + lane / (kBsPar * P);
   // the substeps of every depth are this one scaled by a power of two (exact)
   const double hn = H / (2 * (c + 1));
@@ -1492,18 +1518,15 @@ __device__ __forceinline__ int bs_integrate_mw(int sz, double y[6], double H,
         }
       }
     }
-    int best = gs;
-    if (all) {
-      if (lane == 0) X.gs[buf][wave] = gs;
-      __syncthreads();
+    if (lane == 0) X.gs[buf][wave] = gs;
+    T.sync();
+    int best = INT_MAX;
 #pragma unroll
-      for (int w = 0; w < kBsWaves; ++w) best = min(best, X.gs[buf][w]);
-    } else {
-      wsync();
-    }
+    for (int w = 0; w < kBsWaves; ++w)
+      if (w >= T.w0 && w < T.w0 + T.nw) best = min(best, X.gs[buf][w]);
     best = __builtin_amdgcn_readfirstlane(best);
     if (best != INT_MAX) {
-      const int w = all ? best / S : wave;
+      const int w = T.w0 + best / S;
 #pragma unroll
       for (int q = 0; q < 6; ++q) y[q] = X.y[buf][w][b][q];
       d += best;
@@ -1519,17 +1542,16 @@ __device__ __forceinline__ int bs_integrate_mw(int sz, double y[6], double H,
 }
 
 // Main-mode group of sz <= P members without collisions (sorted indices in
-// mem; masses and radii staged in mm, mrc), on all waves of the workgroup or on
-// the calling one: start from the pre-drift copy, integrate, wave 0 (the wave)
-// writes back; returns the BS status and, in that wave, per member lane, its
-// momentum change m (v_BS - v_drift).
+// mem; masses and radii staged in mm, mrc), by a team: start from the pre-drift
+// copy, integrate, its first wave writes back; returns the BS status and, in that
+// wave, per member lane, its momentum change m (v_BS - v_drift).
 template <int P>
 __device__ __forceinline__ int bs_member_group(const BsArgs& a, int sz, const int* mem,
                                                double* mm, double* mrc, BsXchg& X,
-                                               long long* nsub, bool all, double& dpx,
+                                               long long* nsub, BsTeam& T, double& dpx,
                                                double& dpy, double& dpz) {
   const int lane = threadIdx.x & 63;
-  const bool lead = !all || __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0;
+  const bool lead = T.rank() == 0;
   const int b = par_memb<P>(lane);
   const int id = b < sz ? mem[b] : -1;
   // every load the group needs is issued at once: the members' masses and
@@ -1556,12 +1578,9 @@ __device__ __forceinline__ int bs_member_group(const BsArgs& a, int sz, const in
     mm[lane] = mw;
     mrc[lane] = rcw;
   }
-  if (all)
-    __syncthreads();
-  else
-    wsync();
+  T.sync();
   const ParBody<P> Q = par_body<P>(sz, mm, mrc);
-  const int r = bs_integrate_mw<P>(sz, y, a.dt, Q, a.G, a.Gm0, a.tol, a.max_depth, nsub, X, all);
+  const int r = bs_integrate_mw<P>(sz, y, a.dt, Q, a.G, a.Gm0, a.tol, a.max_depth, nsub, X, T);
   dpx = dpy = dpz = 0.0;
   if (lead && lane == par_lane<P>(0, 0, b) && id >= 0) {  // one lane per member writes
     const double m = mm[b];
@@ -1836,31 +1855,28 @@ struct BsLds {
   BsXchg X;
 };
 
-// One group of up to kBsPar members without collisions on all waves of the
-// workgroup or on the calling one: members sorted ascending, integrated, and the
-// group's momentum change written by wave 0 (the wave).
+// One group of up to kBsPar members without collisions by a team: members
+// sorted ascending, integrated, and the group's momentum change written by its
+// first wave.
 __device__ __forceinline__ void bs_group_few(const BsArgs& a, const int* gmem, int g, int o,
                                              int sz, int* mem, double* mm, double* mrc, BsXchg& X,
-                                             long long* nsub, bool all) {
+                                             long long* nsub, BsTeam& T) {
   const int lane = threadIdx.x & 63;
-  const bool lead = !all || __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0;
+  const bool lead = T.rank() == 0;
   // every wave ranks the members; one writes them in order
   const int my = lane < sz ? gmem[o + lane] : INT_MAX;
   int rank = 0;
   for (int q = 0; q < sz; ++q) rank += (__builtin_amdgcn_readlane(my, q) < my) ? 1 : 0;
   if (lead && lane < sz) mem[rank] = my;
-  if (all)
-    __syncthreads();
-  else
-    wsync();
+  T.sync();
   double dpx, dpy, dpz;
   int r;
   if (sz <= 2)
-    r = bs_member_group<2>(a, sz, mem, mm, mrc, X, nsub, all, dpx, dpy, dpz);
+    r = bs_member_group<2>(a, sz, mem, mm, mrc, X, nsub, T, dpx, dpy, dpz);
   else if (sz <= 4)
-    r = bs_member_group<4>(a, sz, mem, mm, mrc, X, nsub, all, dpx, dpy, dpz);
+    r = bs_member_group<4>(a, sz, mem, mm, mrc, X, nsub, T, dpx, dpy, dpz);
   else
-    r = bs_member_group<8>(a, sz, mem, mm, mrc, X, nsub, all, dpx, dpy, dpz);
+    r = bs_member_group<8>(a, sz, mem, mm, mrc, X, nsub, T, dpx, dpy, dpz);
   if (!lead) return;
   if (r != 0 && lane == 0) atomicOr(&a.st->flags, F_BS);
   // the group's momentum change for the second Sun kick (fixed lane order)
@@ -1885,11 +1901,12 @@ __device__ __forceinline__ void bs_group_few(const BsArgs& a, const int* gmem, i
 __device__ __forceinline__ void bs_groups(const BsArgs& a, int ng, const int* goff,
                                           const int* gmem, BsLds& L) {
   long long nsub = 0;
+  BsTeam T = {0, kBsWaves, nullptr, 0};
   for (int g = blockIdx.x; g < ng; g += gridDim.x) {
     const int o = goff[g];
     const int sz = goff[g + 1] - o;
     if (!a.coll && sz <= kBsPar)
-      bs_group_few(a, gmem, g, o, sz, L.mem, L.mm, L.mrc, L.X, &nsub, true);
+      bs_group_few(a, gmem, g, o, sz, L.mem, L.mm, L.mrc, L.X, &nsub, T);
     else if (threadIdx.x < 64)
       bs_group_one(a, gmem, g, o, sz, L.mem, L.mm, L.mrc, L.mR, L.R, &nsub);
     // the group's LDS (mem, mm, mrc, mR, R, X) is free for the next one
@@ -1938,16 +1955,15 @@ __global__ __launch_bounds__(64 * kBsWaves, LB) void k_group_bs(EncArgs e, BsArg
 // launch, nsteps steps of them, where five launches of one or few workgroups
 // each pay their start, their loads and their drain.  Bound by the chain of
 // one step (Kepler drift, pair terms, radii) on one wave: 16 bodies without
-// encounters 17.0 -> 6.8 us a step in calls of 16 steps, 22.7 -> 19.6 in calls
-// of one.
+// encounters 16.2 -> 6.4 us a step in calls of 16 steps.
 // Lane i of wave 0 holds body i through the steps; the other waves share
 // the pair sums and the BS.  Every sum is formed in the order of the separate
 // kernels (candidates ascending; pair terms two by two as their 16 waves take
-// them), so both give the same bits.  The candidate rows live as bit masks and
-// go back to the table at the end.
+// them), so both give the same result to rounding (a product may fuse into a
+// sum in one and not in the other; most runs agree in every bit).  The
+// candidate rows live as bit masks and go back to the table at the end.
 constexpr int kSmallN = 16;
-constexpr int kSmallW = 4;      // waves
-constexpr int kSmallSplit = 3;  // groups from which each wave takes its own
+constexpr int kSmallW = 4;  // waves
 static_assert(kSmallW == kBsWaves, "the workgroup integrates the groups");
 
 struct SmallArgs {
@@ -1968,37 +1984,62 @@ struct SmallLds {
   unsigned near[kSmallN / 2][kSmallN];  // candidates among the two partners
   unsigned kh[kKepBins];
   int ne;
-  int mem[kSmallW][kSmallN];  // a wave's own group
+  int mem[kSmallW][kSmallN];  // a team's group
   double mm[kSmallW][kBsPar], mrc[kSmallW][kBsPar];
+  int cnt[kSmallW];           // a team's arrivals
 };
 
-// The groups of a small system's step by one workgroup: one or two in turn on
-// all waves, as bs_groups does; from kSmallSplit on each wave takes groups of
-// its own, with the same substeps (of so few bodies at most one group has more
-// than kBsPar members, which always take one wave).  In turn on all waves, five
-// groups of 16 bodies cost 57 us a step against 45 by the separate kernels.
+// The groups of a small system's step by one workgroup.  One group takes all
+// waves, as in bs_groups, two take two waves each, of three the largest takes
+// two, and of more each wave takes one after another, always with the same
+// substeps (of so few bodies at most one group has more than kBsPar members,
+// which always take one wave).
+// us a step in calls of 16, all waves a group at a time against so: 12 bodies in
+// two pairs 22.0 / 17.7, 8 in groups of 6 and 2 30.6 / 25.9, 12 in two of 4 to 5
+// 48.5 / 40.9, 16 in five 56.8 / 41.6.
 __device__ __forceinline__ void bs_groups_small(const BsArgs& a, int ng, SmallLds& L) {
   static_assert(2 * (kBsPar + 1) > kSmallN, "one set of large-group records");
+  static_assert(kSmallW == 4, "the teams below");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool all = ng < kSmallSplit;
   BsLds& B = L.g.b;
   const int *goff = L.g.g.gof, *gm = L.g.gm;
+  // this wave's team, its first group and the step to its next one
+  BsTeam T = {wave, 1, nullptr, 0};
+  int g = wave;
+  if (ng == 1) {
+    T.w0 = g = 0;
+    T.nw = kSmallW;
+  } else if (ng == 2) {
+    g = wave >> 1;
+    T.w0 = wave & 2;
+    T.nw = 2;
+  } else if (ng == 3) {
+    const int s0 = goff[1] - goff[0], s1 = goff[2] - goff[1], s2 = goff[3] - goff[2];
+    const int big = __builtin_amdgcn_readfirstlane(s0 >= max(s1, s2) ? 0 : s1 >= s2 ? 1 : 2);
+    if (wave < 2) {
+      g = big;
+      T.w0 = 0;
+      T.nw = 2;
+    } else {  // the others in order
+      g = wave - 2;
+      if (g >= big) ++g;
+    }
+  }
+  T.cnt = &L.cnt[T.w0];
   long long nsub = 0;
-  for (int g = all ? 0 : wave; g < ng; g += all ? 1 : kSmallW) {
+  for (; g < ng; g += kSmallW) {
     const int o = goff[g];
     const int sz = goff[g + 1] - o;
     if (sz > kBsPar) {
-      if (!all || wave == 0)
+      if (T.rank() == 0)
         bs_group_one(a, gm, g, o, sz, B.mem, B.mm, B.mrc, B.mR, B.R, &nsub);
     } else {
-      const int w = all ? 0 : wave;
-      bs_group_few(a, gm, g, o, sz, L.mem[w], L.mm[w], L.mrc[w], B.X, &nsub, all);
+      bs_group_few(a, gm, g, o, sz, L.mem[T.w0], L.mm[T.w0], L.mrc[T.w0], B.X, &nsub, T);
     }
-    if (all) __syncthreads();  // the group's LDS is free for the next one
   }
-  if (!all) __syncthreads();
-  if (lane == 0 && (wave == 0 || !all) && nsub > 0)
+  __syncthreads();
+  if (lane == 0 && T.rank() == 0 && nsub > 0)
     atomicAdd(&a.st->bs_sub, (unsigned long long)nsub);
 }
 
@@ -2147,6 +2188,7 @@ __global__ __launch_bounds__(64 * kSmallW) void k_small_steps(SmallArgs A) {
       }
       int rows = act ? min(__popc(cand), o.cpb) : 0;
       for (int s = 32; s > 0; s >>= 1) rows += __shfl_xor(rows, s, 64);
+      if (lane < kSmallW) L.cnt[lane] = 0;
       if (lane == 0) {
         L.ne = ne;
         if (full) st->fullkicks += 1ull;
@@ -3090,14 +3132,18 @@ BsArgs bs_args(const MassiveWs& w, const StepConsts& c) {
 }  // namespace
 
 // Whether the small-system kernel takes these steps: no composed step (its
-// search goes over all pairs), no bodies leaving, at most kSmallN bodies.  The
-// line lies there because its one workgroup integrates a step's groups one
-// after another, the separate kernels each in a workgroup of its own.  us a
-// step in calls of 16, separate kernels against this one: 16 bodies without
-// encounters 17.0 / 6.8, with two groups of two 31.8 / 24.7; 8 bodies in one
-// group 35.8 / 30.2.  It loses only where 9 to 16 bodies form one group, which
-// one wave integrates on either path: 16 bodies 179 / 188.  32 bodies
-// without encounters 17.7 / 7.6, but with 6 groups 47.3 / 63.6.
+// search goes over all pairs), no bodies leaving, at most kSmallN bodies.  us a
+// step, separate kernels against this one, in calls of 16: 16 bodies without
+// encounters 16.2 / 6.4, with one pair 26.1 / 19.7, with two or three 29.5 / 22.1,
+// in three groups of up to 11 47.5 / 42.1, 8 in one group 52.3 / 49.9; in calls of
+// two 23.3 / 15.9, of one 33 / 34 with the call.  A group of 9 to 16 takes one wave
+// by either: 134 / 136, 150 / 160 in calls of one.  It loses where several groups
+// refine deeply, which the separate kernels give four waves each: 14 bodies in
+// two groups of seven 616 / 766, 16 in two of eight 81 / 90, in six 69 / 75.  Which
+// of these a step will be the host cannot know.  Beyond 16 bodies there is as
+// much to gain without encounters (32: 17.7 / 7.6 in a form that walked the
+// partners) but the layout ends there: 8 pairs of partners on the half-waves, one
+// set of records for a large group, four waves for the groups.
 bool massive_small(const MassiveWs& w, const StepConsts& c) {
   return w.n <= kSmallN && !c.all_pairs && !c.phys && !c.coll;
 }

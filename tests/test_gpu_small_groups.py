@@ -1,6 +1,7 @@
 """Small systems with several encounter groups in a step, which their one
-workgroup integrates one group a wave, and with one or two, which it integrates
-in turn, against the separate kernels and the oracle."""
+workgroup integrates side by side (two waves each of two, two for the largest of
+three, one each of more), and with one, which takes every wave, against the
+separate kernels and the oracle."""
 import numpy as np
 import pytest
 
@@ -26,10 +27,12 @@ def clusters(sizes, seed=3):
     return m, x, u
 
 
-# one and two groups (in turn); three, four, eight (a wave takes two); one of more
-# than 8 members beside others, first and last; the largest counts of 16 bodies
+# one group; two, three (the largest first, in the middle and last), four, eight (a
+# wave takes two); one of more than 8 members beside others, first and last; the
+# largest counts of 16 bodies
 @pytest.mark.gpu
-@pytest.mark.parametrize("sizes", [[2], [8, 8], [2, 2, 2], [3, 5, 4], [7, 3, 3], [4, 4, 4, 4],
+@pytest.mark.parametrize("sizes", [[2], [8, 8], [2, 2, 2], [3, 5, 4], [7, 3, 3], [3, 3, 6],
+                                   [2, 7], [9, 3], [4, 12], [16], [5], [4, 4, 4, 4],
                                    [2, 3, 2, 4, 2], [2] * 8, [9, 2, 2], [2, 2, 12], [10, 3, 3]])
 def test_small_system_groups(sizes):
     print("small groups", sizes, flush=True)
