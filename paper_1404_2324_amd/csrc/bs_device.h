@@ -463,7 +463,8 @@ constexpr BsWeights bs_weights() {
 static __constant__ BsWeights kBsW = bs_weights();
 
 // Column that the first attempt of a group tests first; later ones start at
-// the column the last one accepted.
+// the column the last one accepted.  2 and 4 are as good within 2 % (64 steps of
+// 2048 bodies 3875, 3892 and 3908 us with 2, 3 and 4; 32 of 777 1140, 1113, 1113).
 constexpr int kBsFirstCol = 3;
 
 // One speculative round: returns the accepted depth offset (0..S-1), with the

@@ -89,7 +89,10 @@ __device__ __forceinline__ double rcp_nr(double x) {
 // or root from the refined reciprocal (root), corrected by its exact residual.
 // 8 and 10 instructions where the general forms, which scale their operands
 // first, take 11 and 19.  Measured on gfx950 against them over 16M arguments
-// each: every result the same.
+// each: every result the same (sampled, no bound proved).  An infinite or zero
+// divisor or radicand gives NaN, where the general forms give 0 or infinity:
+// callers whose operands can overflow (a distance past 1e154, its cube past
+// 1e102) take those.
 __device__ __forceinline__ double div_nr(double a, double b) {
   const double y = rcp_nr(b);
   const double q = a * y;
@@ -208,9 +211,12 @@ __device__ __forceinline__ void stumpff(double z, double& c0, double& c1,
 // s = t - eta0 t^2/(2 r0) + (eta0^2/2 - r0 zeta0/6) t^3/r0^2 with t = dt/r0,
 // when its corrections are small against t (short steps); otherwise s = t.
 // The Stumpff values of the last residual evaluation are reused for f and g
-// when the iteration stopped there; 1/r0 and 1/r are formed once and
-// multiplied in; roots and quotients by the short forms above (the same bits).  Returns the iteration count, or a
-// negative count when max_iter was reached without convergence.
+// when the iteration stopped there; 1/r0 and 1/r are formed once by rcp_nr
+// (correctly rounded over 8M arguments) and multiplied in; the root and quotient
+// of the iteration and r0 by sqrt_nr and div_nr.  r0 past 1e154, or a derivative
+// that large in a grazing hyperbolic drift, makes them NaN, and the iteration
+// does not converge.  Returns the iteration count, or a negative count when
+// max_iter was reached without convergence.
 // s_out (optional) receives the converged universal anomaly s.
 __device__ __forceinline__ int kepler_drift(double mu, double dt, double& x,
                                             double& y, double& z, double& vx,
@@ -275,7 +281,10 @@ __device__ __forceinline__ int kepler_drift(double mu, double dt, double& x,
 // Minimum over t in [0,1] of the cubic Hermite interpolant of the squared
 // separation; the stationary points solve a t^2 + b t + c = 0 with
 // a = 6(P0-P1) + 3 dt (Pd0+Pd1) (derivative of Eq. 10; the printed sign of
-// the Pd1 term is a typo), b = 6(P1-P0) - 2 dt (2 Pd0 + Pd1), c = dt Pd0.
+// the Pd1 term is a typo), b = 6(P1-P0) - 2 dt (2 Pd0 + Pd1), c = dt Pd0.  Roots
+// and quotients by sqrt_nr and div_nr; where they overflow (separations past
+// 1e76) the stationary points are NaN and lie, as the infinite ones of the general
+// forms, outside (0, 1).
 __device__ __forceinline__ double hermite_P(double t, double dt, double P0,
                                             double P1, double Pd0, double Pd1) {
   const double u = 1.0 - t;
