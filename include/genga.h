@@ -393,9 +393,10 @@ int genga_bodies(genga_ctx *ctx, int32_t *h_id, int64_t cap, int32_t *h_nlive, d
 
 /* Bytes of the caller's buffer for nsteps steps with a checkpoint every
  * ckpt_every steps (the checkpoints plus the backward pass's workspace: one
- * segment's tape, and for the hybrid map the starts of a group's accepted BS
- * substeps and the positions of one Gragg sequence); 0 when the context
- * supports neither map or the arguments are invalid. */
+ * segment's tape, 7 doubles per body and step or 21 for the hybrid map, and for
+ * that map the starts of 128 accepted BS substeps of every body and the
+ * positions of one Gragg sequence); 0 when the context supports neither map or
+ * the arguments are invalid. */
 size_t genga_adj_buffer_bytes(genga_ctx *ctx, int64_t nsteps, int ckpt_every);
 
 /* Advance every system nsteps steps of the context's map, keeping the state

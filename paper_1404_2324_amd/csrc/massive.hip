@@ -1925,7 +1925,7 @@ __device__ __forceinline__ void bs_groups(const BsArgs& a, int ng, const int* go
 // Test-particle mode (up to 32 planets) runs it beside the particles'
 // refinement, whose waves hold half the registers of the SIMDs they are on:
 // LB = 2 and the small tables let it start at once, where the 2048-body form
-// (356 registers, 90 KB of LDS) waited for four free SIMDs on one compute unit.
+// (354 registers, 90 KB of LDS) waited for four free SIMDs on one compute unit.
 template <int N, int NP>
 struct GroupBsLds {
   GroupLds<64 * kBsWaves, N, NP> g;
@@ -3264,9 +3264,9 @@ hipError_t accel_run(const MassiveWs& w, const StepConsts& c, const double* m, c
 // and candidate counts of up to kNoAllocBodies bodies (116 bytes per padded
 // body), the 64-body chunks' largest thresholds and the pair kernel's partial sums
 // (6 doubles x splits x padded bodies, splits x padded bodies <=
-// kPairTargetBig, the pair kernel's shape being the workspace path's): 8.2 MB.  Each GPU holds its own copy until the process ends;
-// every call on a GPU uses that GPU's copy, so calls that overlap on one GPU
-// race.  Every byte a call reads is written earlier in the same call.
+// kPairTargetBig, the pair kernel's shape being the workspace path's): 8.2 MB.
+// Each GPU holds its own copy until the process ends; every call on a GPU uses
+// that GPU's copy, so calls that overlap on one GPU race.  Every byte a call reads is written earlier in the same call.
 constexpr int kNoAllocBodies = kAccelNoAllocMax;
 static_assert(kNoAllocBodies % 256 == 0, "bodies are padded to multiples of 256");
 static_assert(kNoAllocBodies <= kPairTarget && kPairTarget <= kPairTargetBig,

@@ -953,11 +953,14 @@ TpArgs tp_args(const MassiveWs& w, const TpWs& t, const StepConsts& c, int k, bo
 }  // namespace
 
 // With few particles the refinement is short and the two passes over the queue
-// and the branch cost more than it: one branch.  us a step in graphs of 16, two
-// branches against one: 10^6 particles and 8 planets 215 against 289 (310 before,
-// with a one-workgroup scan of the lists), 10^5 152 / 168, 10^4 98 / 114 and 93 /
-// 104 (two draws), 3001 particles and 3 planets 84 / 94 and 69 / 49, 1000
-// particles 85 / 79.
+// and the branch cost more than it: one branch.  Eight steps in us, one branch
+// against two: 8 planets and 1000 particles 418 / 552, 3000 602 / 627, 5000 682 /
+// 654, 8192 709 / 670, 10^5 833 / 757, 10^6 1707 / 1373; 3 planets and 3000 426 / 548,
+// 5000 662 / 568, 8192 642 / 583, 10^6 1809 / 1476.  What it trades is the queue's
+// length, which the host does not know: where half of the particles meet a
+// planet two branches are the faster from 1000 particles on (907 / 750; 8192 981 /
+// 813, 10^5 2225 / 1735).  The line is where they are so for ordinary systems, with
+// a margin.
 bool tp_two_branches(int64_t ntp, int encounter_free) {
   constexpr int64_t kTpOverlap = 8192;
   return ntp >= kTpOverlap && !encounter_free;
