@@ -31,10 +31,11 @@ __device__ __forceinline__ double one_minus(double K) {
 // dv/dt of H_A for the lane's body: the fixed star plus the (1-K) part of the
 // group's pair terms (Eq. 1 gradient); other members' data by lane reads.
 // Partners go two by two: their terms are independent chains, computed without
-// branches (a far or absent partner's is set to zero).  Bound by that chain
+// branches (a far or absent partner's weight is set to zero, and its separation
+// too where one is not finite, for the product not to be NaN).  Bound by that chain
 // (one wave on its SIMD): a partner at a time, with a branch at each test,
-// took 171 us a step for 16 bodies in one group and 192 for 17, this takes 137
-// and 149 (64 bodies 988 -> 802).  FK: which product of the pair's weight fuses
+// took 171 us a step for 16 bodies in one group and 192 for 17, this takes 139
+// and 153 (64 bodies 988 -> 815).  FK: which product of the pair's weight fuses
 // into the other's sum; both forms are kept for the bits of their callers (deep
 // passages amplify a last bit).
 template <bool FK>
@@ -54,7 +55,7 @@ __device__ __forceinline__ void ha_accel(int sz, int lane, double x, double y,
     bool near[U], any = false;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int j = j0 + u;  // at most 63: sz <= 64
+      const int j = j0 + u;  // at most 63: sz <= 64; beyond sz an idle lane
       dx[u] = readlane_d(x, j) - x;
       dy[u] = readlane_d(y, j) - y;
       dz[u] = readlane_d(z, j) - z;
@@ -66,6 +67,11 @@ __device__ __forceinline__ void ha_accel(int sz, int lane, double x, double y,
       any = any || near[u];
     }
     if (__builtin_amdgcn_ballot_w64(any) == 0ull) continue;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(q2[0] + q2[1] < 1e300)) != 0ull, 0)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (!near[u]) dx[u] = dy[u] = dz[u] = 0.0;
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const double iq = rsqrt_nr(q2[u]);
