@@ -142,7 +142,7 @@ enum { KICK_CLOSE = 0, KICK_INIT = 1, KICK_ACC = 2 };
 // against the wave's largest threshold T (over its 64 bodies and its partner
 // range, from the 64-body chunk maxima); a wave with any lane below it takes
 // the exact test pair by pair.  Bound from 5000 bodies on by FP64 issue (18
-// vector instructions a pair and the reciprocal root's estimate).  The
+// vector instructions a pair, the reciprocal root's estimate one of them).  The
 // W waves' sums are added in LDS in wave order; the split's sums go to pp.
 template <int MODE, int W>
 __global__ __launch_bounds__(W * 64) void k_pair_part(PairArgs a,
